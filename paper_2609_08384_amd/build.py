@@ -11,11 +11,12 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libbrahms.so")
 
-# the pass kernels of the heaviest line lengths first (the longest compiles),
-# then the host logic
-SOURCES = ["len_144.hip", "len_72.hip", "len_256.hip", "len_96.hip", "len_9_18.hip", "len_192.hip",
-           "len_128.hip", "len_48_64.hip", "len_24_32.hip", "len_small.hip", "len_long.hip", "engine.hip",
-           "adjoint.hip", "batch.hip", "diag.hip", "noalloc.hip"]
+# the pass kernels first, one unit per line length or a few short ones (the
+# longest compiles in front), then the host logic
+SOURCES = ["len_144.hip", "len_72.hip", "len_96.hip", "len_256.hip", "len_192.hip", "alt_48.hip", "alt_24.hip",
+           "len_128.hip", "len_36.hip", "alt_64.hip", "alt_32.hip", "len_48.hip", "len_64.hip", "len_9_18.hip",
+           "len_24.hip", "len_32.hip", "alt_8_12.hip", "alt_16.hip", "len_16.hip", "len_8_12.hip",
+           "len_1_to_6.hip", "len_long.hip", "engine.hip", "adjoint.hip", "batch.hip", "diag.hip", "noalloc.hip"]
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared",
     "--offload-arch=gfx950",

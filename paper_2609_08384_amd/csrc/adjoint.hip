@@ -52,8 +52,7 @@ constexpr int kSetRows = kChunk / 2;   // table rows of the second set start her
 int pass_blocks(int axis, const brahms_plan_s& p) {
   const int n = axis == AX_X ? p.nx : p.nt;
   const long lines = axis == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
-  const int lpb = lines_per_block(n);
-  return int((lines + lpb - 1) / lpb);
+  return brahms::detail::adjoint_blocks(axis, lines, n);
 }
 
 AdjLayout adj_layout(const brahms_plan_s& p, int nsteps, int every) {

@@ -28,13 +28,14 @@ template <int NF>
 __device__ inline void chi2_products_vjp(const float2* y, const float2* gq, float2* gy) {
   if constexpr (NF == 3) {
     // Q_p = s i, Q_s = p conj(i), Q_i = p conj(s)
-    gy[0] = cadd(cmul(y[2], gq[1]), cmul(y[1], gq[2]));
-    gy[1] = cadd(cmulc(gq[0], y[2]), cmulc(y[0], gq[2]));
-    gy[2] = cadd(cmulc(gq[0], y[1]), cmulc(y[0], gq[1]));
+    gy[0] = cfma(cmul(y[2], gq[1]), y[1], gq[2]);
+    gy[1] = cfmac(cmulc(gq[0], y[2]), y[0], gq[2]);
+    gy[2] = cfmac(cmulc(gq[0], y[1]), y[0], gq[1]);
   } else {
     // Q_F = S conj(F), Q_S = F F
     const float2 t = cmulc(gq[1], y[0]);  // gS conj(F)
-    gy[0] = cadd(cmulc(y[1], gq[0]), make_float2(2.f * t.x, 2.f * t.y));
+    const float2 u = cmulc(y[1], gq[0]);
+    gy[0] = make_float2(fmaf(2.f, t.x, u.x), fmaf(2.f, t.y, u.y));
     gy[1] = cmul(y[0], gq[0]);
   }
 }
@@ -48,7 +49,7 @@ __device__ inline float phase_term(const float2* g, const float2 (*co)[kNlCoef],
   for (int j = 0; j < NF; ++j) {
     const float2 w = cmul(co[j][k], q[j]);
     // Re(conj(g) i w) = g.x * (-w.y) + g.y * w.x
-    s += sigma[j] * (g[j].y * w.x - g[j].x * w.y);
+    s = fmaf(sigma[j], fmaf(g[j].y, w.x, -(g[j].x * w.y)), s);
   }
   return s;
 }
@@ -85,21 +86,21 @@ __device__ inline void rk4_vjp_point(const float2* y, float2* g, const float2 (*
 #pragma unroll
   for (int j = 0; j < NF; ++j) {
     gy[j] = cadd(gout[j], gys[j]);
-    gq[j] = cadd(cmulc(gys[j], co[j][2]), cmulc(gout[j], co[j][4]));  // conj(a3) g_ys3 + conj(b2) g'
+    gq[j] = cfmac(cmulc(gys[j], co[j][2]), gout[j], co[j][4]);  // conj(a3) g_ys3 + conj(b2) g'
   }
   chi2_products_vjp<NF>(ys2, gq, gys);                                   // g of ys2
   pm += phase_term<NF>(gys, co, 1, q2, sigma);
 #pragma unroll
   for (int j = 0; j < NF; ++j) {
     gy[j] = cadd(gy[j], gys[j]);
-    gq[j] = cadd(cmulc(gys[j], co[j][1]), cmulc(gout[j], co[j][4]));  // conj(a2) g_ys2 + conj(b2) g'
+    gq[j] = cfmac(cmulc(gys[j], co[j][1]), gout[j], co[j][4]);  // conj(a2) g_ys2 + conj(b2) g'
   }
   chi2_products_vjp<NF>(ys1, gq, gys);                                   // g of ys1
   pa += phase_term<NF>(gys, co, 0, q1, sigma);
 #pragma unroll
   for (int j = 0; j < NF; ++j) {
     gy[j] = cadd(gy[j], gys[j]);
-    gq[j] = cadd(cmulc(gys[j], co[j][0]), cmulc(gout[j], co[j][3]));  // conj(a1) g_ys1 + conj(b1) g'
+    gq[j] = cfmac(cmulc(gys[j], co[j][0]), gout[j], co[j][3]);  // conj(a1) g_ys1 + conj(b1) g'
   }
   chi2_products_vjp<NF>(y, gq, gys);
 #pragma unroll
@@ -117,7 +118,7 @@ __device__ inline void rk4_vjp_point(const float2* y, float2* g, const float2 (*
 //   VJP_LAST:  the pass undoes the first pass of a forward step: FFT .
 //              conj(P) . IFFT, then reverse RK4 with the step's input.
 // g is updated in place; the block's three dJ/dPhi partial sums (fixed-order
-// tree reduction in double) go to dphi_out[block].
+// reduction in double) go to dphi_out[block].
 // ---------------------------------------------------------------------------
 enum VjpWhere { VJP_FIRST = 1, VJP_LAST = 2 };
 
@@ -135,42 +136,47 @@ struct AdjArgs {
   float sigma[3];
 };
 
-template <int N1, int N2, int AX, int NF, int AT, bool FULL>
+// The block's three dJ/dPhi sums, in a fixed order: a tree within each of
+// its groups of T threads, then the groups in turn.
+template <int BLOCK, int T>
+__device__ __forceinline__ void reduce_dphi(const double* dphi, double (*s_red)[BLOCK], double* out) {
+  const int tid = threadIdx.x, g = tid % T;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s_red[k][tid] = dphi[k];
+  __syncthreads();
+  for (int w = T / 2; w > 0; w >>= 1) {
+    if (g < w)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s_red[k][tid] += s_red[k][tid + w];
+    __syncthreads();
+  }
+  if (tid < 3) {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < BLOCK / T; ++i) s += s_red[tid][i * T];
+    out[blockIdx.x * 3 + tid] = s;
+  }
+}
+
+template <int N1, int N2, int AX, int NF, int AT>
 __global__ __launch_bounds__(kBlock) void adjoint_pass(AdjArgs args) {
   using G = LineGeom<N1, N2>;
   constexpr int N = G::N;
+  constexpr bool REG = twiddle_registers<N1, NF, kBlock>();
+  static_assert(AX == AX_X || AX == AX_T, "RK4 reverse sweeps live in the x or tau pass");
   __shared__ float2 lds[G::LDS_ELEMS];
   __shared__ float2 s_tw[N];
   __shared__ float2 s_prop[NF * N];
-  __shared__ double s_red[kBlock];
+  __shared__ double s_red[3][kBlock];
 
   const int tid = threadIdx.x;
-  for (int i = tid; i < N; i += kBlock) s_tw[i] = args.tw[i];
-  for (int i = tid; i < NF * N; i += kBlock)
-    s_prop[i] = args.prop[(i / N) * args.field_stride + args.axis_off + i % N];
-
-  int t, li;
-  unsigned base, estride;
-  bool valid = true;
-  if constexpr (AX == AX_X) {
-    t = tid % N2;
-    li = tid / N2;
-    const unsigned line = blockIdx.x * unsigned(G::LPB) + li;
-    if constexpr (!FULL) valid = line < unsigned(args.ny) * unsigned(args.nt);
-    base = line * unsigned(args.nx);
-    estride = 1;
-  } else {
-    static_assert(AX == AX_T, "RK4 reverse sweeps live in the x or tau pass");
-    li = tid % G::LPB;
-    t = tid / G::LPB;
-    const unsigned tile = unsigned((unsigned long long)blockIdx.x * args.tile_mul % gridDim.x);
-    const unsigned q = tile * unsigned(G::LPB) + li;
-    if constexpr (!FULL) valid = q < unsigned(args.nx) * unsigned(args.ny);
-    base = q;
-    estride = unsigned(args.nx) * unsigned(args.ny);
-  }
-  const unsigned idx0 = base + unsigned(t) * estride;
-  const unsigned estep = unsigned(N2) * estride;
+  const int t = AX == AX_X ? tid % N2 : tid / G::LPB;
+  const int li = AX == AX_X ? tid / N2 : tid % G::LPB;
+  unsigned bx = blockIdx.x;
+  if constexpr (AX == AX_T) bx = unsigned((unsigned long long)bx * args.tile_mul % gridDim.x);
+  const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
+  const unsigned idx0 = la.base + unsigned(t) * la.estride;
+  const unsigned estep = unsigned(N2) * la.estride;
   // x lines: a line's N2 lanes are consecutive threads, within one wavefront
   constexpr bool WL = AX == AX_X && N2 <= 64 && 64 % N2 == 0;
   // a line's LDS row (lines of one lane exchange nothing: no row)
@@ -188,22 +194,23 @@ __global__ __launch_bounds__(kBlock) void adjoint_pass(AdjArgs args) {
   }
   // RK4 coefficients: the same for every thread, in scalar registers
   float2 co[NF][kNlCoef];
-#pragma unroll
-  for (int j = 0; j < NF; ++j)
-#pragma unroll
-    for (int c = 0; c < kNlCoef; ++c) co[j][c] = wave_uniform(args.nl[j * kNlCoef + c]);
+  load_coefficients<NF>(args.nl, co);
   float sigma[NF];
 #pragma unroll
   for (int j = 0; j < NF; ++j) sigma[j] = args.sigma[j];
   double dphi[3] = {0.0, 0.0, 0.0};
 
+  StageTables<N, NF, kBlock, false> st;
+  st.begin(args, 0, tid);
   float2 v[NF][N1];
 #pragma unroll
   for (int j = 0; j < NF; ++j)
 #pragma unroll
-    for (int e = 0; e < N1; ++e)
-      v[j][e] = valid ? load_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes) : make_float2(0.f, 0.f);
+    for (int e = 0; e < N1; ++e) v[j][e] = load_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes);
+  st.end(false, tid, s_tw, s_prop, s_tw, s_prop);
   __syncthreads();  // s_tw, s_prop staged
+  LaneTwiddles<N1, N2, REG> tw;
+  tw.init(s_tw, t);
 
   auto reverse_rk4 = [&]() {
 #pragma unroll
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(kBlock) void adjoint_pass(AdjArgs args) {
       float2 yy[NF], gg[NF];
 #pragma unroll
       for (int j = 0; j < NF; ++j) {
-        yy[j] = valid ? load_slot<false>(ry[j], lane_bytes, unsigned(e) * slot_bytes) : make_float2(0.f, 0.f);
+        yy[j] = load_slot<false>(ry[j], lane_bytes, unsigned(e) * slot_bytes);
         gg[j] = v[j][e];
       }
       // One point at a time: tie this point's inputs to the phase sums of the
@@ -228,33 +235,106 @@ __global__ __launch_bounds__(kBlock) void adjoint_pass(AdjArgs args) {
   };
 
   if constexpr (AT == VJP_FIRST) reverse_rk4();
-#pragma unroll
-  for (int j = 0; j < NF; ++j) {
-    line_fft<N1, N2, false, WL>(v[j], t, lbuf, s_tw, K);
-#pragma unroll
-    for (int e = 0; e < N1; ++e) v[j][e] = cmulc(v[j][e], s_prop[j * N + t + N2 * e]);
-    line_fft<N1, N2, true, WL>(v[j], t, lbuf, s_tw, K);
-  }
+  line_trip<N1, N2, NF, WL, true>(v, tw, t, lbuf, s_prop, K);
   if constexpr (AT == VJP_LAST) reverse_rk4();
-  if (valid) {
+  if (la.valid) {
 #pragma unroll
     for (int j = 0; j < NF; ++j)
 #pragma unroll
       for (int e = 0; e < N1; ++e) store_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
+  } else {
+    dphi[0] = dphi[1] = dphi[2] = 0.0;   // a line past the last one counts for nothing
   }
+  reduce_dphi<kBlock, kBlock>(dphi, s_red, args.dphi_out);
+}
 
-  // block reduction of the three phase derivatives, fixed order
+// The adjoint pass with one field per thread (see axis_pass_split_body): the
+// saved half-step inputs of a thread's points are loaded at the start, with
+// its cotangents.  128 x 128 x 64 and two fields: see narrow_launch.
+template <int N1, int N2, int AX, int NF, int AT>
+__global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass_split(AdjArgs args) {
+  constexpr int T = split_threads(N2, AX), BLOCK = NF * T;
+  using G = LineGeom<N1, N2, T>;
+  constexpr int N = G::N;
+  constexpr bool WL = AX == AX_X && T == 64 && N2 <= 64 && 64 % N2 == 0;
+  static_assert(AX == AX_X || AX == AX_T, "RK4 reverse sweeps live in the x or tau pass");
+  constexpr int XS = N2 > 1 ? G::LDS_ELEMS : N1 * T;
+  __shared__ float2 lds[NF * XS];
+  __shared__ float2 s_tw[N], s_prop[NF * N];
+  __shared__ double s_red[3][BLOCK];
+
+  const int tid = threadIdx.x;
+  const int f = __builtin_amdgcn_readfirstlane(tid / T);
+  const int g = tid % T;
+  const int t = AX == AX_X ? g % N2 : g / G::LPB;
+  const int li = AX == AX_X ? g / N2 : g % G::LPB;
+  const LineAddr la = line_addr<AX, N>(args, blockIdx.x * unsigned(G::LPB) + unsigned(li));
+  const unsigned idx0 = la.base + unsigned(t) * la.estride;
+  const unsigned field_bytes = unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) * 8u;
+  const unsigned lane_bytes = idx0 * 8u, slot_bytes = unsigned(N2) * la.estride * 8u;
+  float2* mine = lds + f * XS;
+  float2* lbuf = (N2 > 1) ? mine + li * G::LSTRIDE : mine;
+  const DftConsts K = *args.consts;
+  float2 co[NF][kNlCoef];
+  load_coefficients<NF>(args.nl, co);
+  float sigma[NF];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    __syncthreads();
-    s_red[tid] = dphi[k];
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-      if (tid < w) s_red[tid] += s_red[tid + w];
-      __syncthreads();
-    }
-    if (tid == 0) args.dphi_out[blockIdx.x * 3 + k] = s_red[0];
+  for (int j = 0; j < NF; ++j) sigma[j] = args.sigma[j];
+  double dphi[3] = {0.0, 0.0, 0.0};
+
+  constexpr int P = (N1 + NF - 1) / NF;
+  StageTables<N, NF, BLOCK, false> st;
+  st.begin(args, 0, tid);
+  const __amdgpu_buffer_rsrc_t rg = field_rsrc(args.g[f], field_bytes);
+  float2 v[N1];
+#pragma unroll
+  for (int e = 0; e < N1; ++e) v[e] = load_slot<false>(rg, lane_bytes, unsigned(e) * slot_bytes);
+  float2 y[P][NF];
+#pragma unroll
+  for (int j = 0; j < NF; ++j) {
+    const __amdgpu_buffer_rsrc_t ry = field_rsrc(args.y[j], field_bytes);
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+      y[k][j] = load_slot<false>(ry, lane_bytes, unsigned(min(f + NF * k, N1 - 1)) * slot_bytes);
   }
+  st.end(false, tid, s_tw, s_prop, s_tw, s_prop);
+  __syncthreads();  // s_tw, s_prop staged
+  LaneTwiddles<N1, N2, true> tw;
+  tw.init(s_tw, t);
+
+  auto reverse_rk4 = [&]() {
+    line_sync<WL>();   // this group's exchange rows are free
+#pragma unroll
+    for (int e = 0; e < N1; ++e) mine[e * T + g] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const int e = f + NF * k;
+      if (N1 % NF == 0 || e < N1) {
+        float2 gg[NF];
+#pragma unroll
+        for (int j = 0; j < NF; ++j) gg[j] = lds[j * XS + e * T + g];
+        rk4_vjp_point<NF>(y[k], gg, co, sigma, dphi);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = gg[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < N1; ++e) v[e] = mine[e * T + g];
+  };
+  float2 (&v1)[1][N1] = reinterpret_cast<float2 (&)[1][N1]>(v);
+
+  if constexpr (AT == VJP_FIRST) reverse_rk4();
+  line_trip<N1, N2, 1, WL, true>(v1, tw, t, lbuf, s_prop + f * N, K);
+  if constexpr (AT == VJP_LAST) reverse_rk4();
+  if (la.valid) {
+#pragma unroll
+    for (int e = 0; e < N1; ++e) store_slot<false>(rg, lane_bytes, unsigned(e) * slot_bytes, v[e]);
+  } else {
+    dphi[0] = dphi[1] = dphi[2] = 0.0;   // a line past the last one counts for nothing
+  }
+  reduce_dphi<BLOCK, T>(dphi, s_red, args.dphi_out);
 }
 
 // Sum the per-block phase derivatives of a segment's adjoint passes (fixed

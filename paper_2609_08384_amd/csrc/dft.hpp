@@ -10,9 +10,16 @@
 // unit_root evaluates roots of unity in double precision (exact quadrant
 // symmetry plus a Taylor series on at most a half quadrant) for the
 // host-side tables.
+//
+// Every multiply-add of the float arithmetic is written out (fmaf) and the
+// compiler's own contraction is switched off: the several kernels that hold
+// one transform (a plan's and a batch's, fields together or one field per
+// thread) then round it alike, bit for bit, whatever surrounds it.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#pragma clang fp contract(off)
 
 namespace brahms {
 
@@ -61,11 +68,15 @@ constexpr void unit_root(long m, long n, double& c, double& s) {
 
 __host__ __device__ inline float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __host__ __device__ inline float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+// (both parts round the product with b.y and fuse the one with b.x, so that
+// the rounding does not tell the real axis from the imaginary one: with the
+// imaginary part's operands swapped, dJ/ddk of the adjoint was off twice as
+// far from its 64-bit value)
 __host__ __device__ inline float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+  return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.y, b.x, a.x * b.y));
 }
 __host__ __device__ inline float2 cmulc(float2 a, float2 b) {  // a * conj(b)
-  return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+  return make_float2(fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -(a.x * b.y)));
 }
 // multiply by -i (forward) or +i (inverse)
 template <bool INV>
@@ -113,8 +124,7 @@ __host__ __device__ inline float2 twiddle_const(float2 a, int m, const DftConsts
       b = INV ? make_float2(K.h * (a.x - a.y), K.h * (a.x + a.y))
               : make_float2(K.h * (a.x + a.y), K.h * (a.y - a.x));
     } else if (rem % 4 == 0 && rem % 12 != 0) {
-      // multiples of 10 degrees (radices with a factor 9), the product's
-      // multiply-adds written out so that every kernel rounds them alike
+      // multiples of 10 degrees (radices with a factor 9)
       switch (rem) {
         case 4: c = K.c36; s = K.s36; break;
         case 8: c = K.c18; s = K.s18; break;
@@ -135,7 +145,7 @@ __host__ __device__ inline float2 twiddle_const(float2 a, int m, const DftConsts
         default: c = K.s12; s = K.c12; break;  // rem == 30
       }
       if (!INV) s = -s;
-      b = make_float2(a.x * c - a.y * s, a.x * s + a.y * c);
+      b = make_float2(fmaf(a.x, c, -(a.y * s)), fmaf(a.x, s, a.y * c));
     }
   }
   if (q == 1) return rot_quarter<INV>(b);
@@ -193,17 +203,13 @@ struct Dft<3, INV> {
     float2 a = v[0];
     float2 t1 = cadd(v[1], v[2]);
     float2 t2 = csub(v[1], v[2]);
-    float2 m = make_float2(a.x - 0.5f * t1.x, a.y - 0.5f * t1.y);
+    const float2 m = make_float2(fmaf(-0.5f, t1.x, a.x), fmaf(-0.5f, t1.y, a.y));
     // forward: X1 = m - i h t2, X2 = m + i h t2
-    float2 r = make_float2(-h * t2.y, h * t2.x);  // i h t2
+    const float2 plus = make_float2(fmaf(-h, t2.y, m.x), fmaf(h, t2.x, m.y));    // m + i h t2
+    const float2 minus = make_float2(fmaf(h, t2.y, m.x), fmaf(-h, t2.x, m.y));
     v[0] = cadd(a, t1);
-    if (INV) {
-      v[1] = cadd(m, r);
-      v[2] = csub(m, r);
-    } else {
-      v[1] = csub(m, r);
-      v[2] = cadd(m, r);
-    }
+    v[1] = INV ? plus : minus;
+    v[2] = INV ? minus : plus;
   }
 };
 
@@ -240,6 +246,30 @@ template <bool INV>
 __host__ __device__ inline float2 mul_mone_i(float2 u) {
   return INV ? make_float2(-u.x - u.y, u.x - u.y) : make_float2(u.y - u.x, -u.y - u.x);
 }
+
+// a0 +- r b (r real), the scaling taken into fused multiply-adds.
+__host__ __device__ inline void radix2_scaled(float2 a0, float r, float2 b, float2& sum, float2& diff) {
+  sum = make_float2(fmaf(r, b.x, a0.x), fmaf(r, b.y, a0.y));
+  diff = make_float2(fmaf(-r, b.x, a0.x), fmaf(-r, b.y, a0.y));
+}
+
+// N = 8 as 4 x 2 (n = 2 n1 + n2, k = k1 + 4 k2), the twiddles h (1 -+ i) and
+// h (-1 -+ i) folded as in the 16-point DFT below: 52 operations.
+template <bool INV>
+struct Dft<8, INV> {
+  __host__ __device__ static inline void run(float2* v, const DftConsts& K) {
+    float2 u[4] = {v[0], v[2], v[4], v[6]}, w[4] = {v[1], v[3], v[5], v[7]};
+    Dft<4, INV>::run(u, K);
+    Dft<4, INV>::run(w, K);
+    v[0] = cadd(u[0], w[0]);
+    v[4] = csub(u[0], w[0]);
+    radix2_scaled(u[1], K.h, mul_one_i<INV>(w[1]), v[1], v[5]);
+    const float2 r = rot_quarter<INV>(w[2]);
+    v[2] = cadd(u[2], r);
+    v[6] = csub(u[2], r);
+    radix2_scaled(u[3], K.h, mul_mone_i<INV>(w[3]), v[3], v[7]);
+  }
+};
 
 // Radix-4 butterfly of the inputs a0, a2 = s b2, a1 = r b1 and a3 = r b3
 // (s, r real), the scalings taken into fused multiply-adds; x[k] =

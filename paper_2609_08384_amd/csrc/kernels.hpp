@@ -104,6 +104,11 @@ __device__ inline float2 cfma(float2 acc, float2 c, float2 q) {  // acc + c q
                      fmaf(c.x, q.y, fmaf(c.y, q.x, acc.y)));
 }
 
+__device__ inline float2 cfmac(float2 acc, float2 a, float2 b) {  // acc + a conj(b)
+  return make_float2(fmaf(a.x, b.x, fmaf(a.y, b.y, acc.x)),
+                     fmaf(a.y, b.x, fmaf(-a.x, b.y, acc.y)));
+}
+
 // A value that is the same in every lane, moved into scalar registers.
 __device__ inline float2 wave_uniform(float2 v) {
   return make_float2(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v.x))),
@@ -201,34 +206,140 @@ __device__ __forceinline__ void line_sync() {
   }
 }
 
-template <int N1, int N2, bool INV, bool WAVE = false>
-__device__ inline void line_fft(float2 (&v)[N1], int t, float2* lbuf, const float2* tw,
-                                const DftConsts& K) {
-  using G = LineGeom<N1, N2>;
+// The lane's inter-stage twiddles exp(-2 pi i t k1 / N): kept in registers
+// for a whole pass (REG: the 2 N1 values are then read from LDS once instead
+// of once per field and direction), or read where they are used.
+template <int N1, int N2, bool REG>
+struct LaneTwiddles {
+  float2 w[REG ? N1 : 1];
+  const float2* tw;
+  int t;
+  __device__ __forceinline__ void init(const float2* table, int lane) {
+    tw = table;
+    t = lane;
+    if constexpr (REG && N2 > 1) {
+#pragma unroll
+      for (int k1 = 1; k1 < N1; ++k1) w[k1] = tw[t * k1];
+    }
+  }
+  __device__ __forceinline__ float2 at(int k1) const {
+    if constexpr (REG) return w[k1];
+    else return tw[t * k1];
+  }
+};
+
+// Stage 1 of a transform: the N1-point DFT and the inter-stage twiddles.
+template <int N1, int N2, bool INV, bool REG>
+__device__ __forceinline__ void line_stage1(float2 (&v)[N1], const LaneTwiddles<N1, N2, REG>& tw,
+                                            const DftConsts& K) {
   dft<N1, INV>(v, K);
   if constexpr (N2 > 1) {
 #pragma unroll
-    for (int k1 = 1; k1 < N1; ++k1) {
-      float2 w = tw[t * k1];
-      if (INV) w.y = -w.y;
-      v[k1] = cmul(v[k1], w);
+    for (int k1 = 1; k1 < N1; ++k1) v[k1] = INV ? cmulc(v[k1], tw.at(k1)) : cmul(v[k1], tw.at(k1));
+  }
+}
+
+// Stage 2, on the values of exchange_get: v[a N2 + n2] -> slot a + (N1/N2) k2.
+template <int N1, int N2, bool INV>
+__device__ __forceinline__ void line_stage2(float2 (&v)[N1], const DftConsts& K) {
+  if constexpr (N2 > 1) {
+    constexpr int R = N1 / N2;
+    float2 o[N1];
+#pragma unroll
+    for (int a = 0; a < R; ++a) {
+      float2 u[N2];
+#pragma unroll
+      for (int n2 = 0; n2 < N2; ++n2) u[n2] = v[a * N2 + n2];
+      dft<N2, INV>(u, K);
+#pragma unroll
+      for (int k2 = 0; k2 < N2; ++k2) o[a + R * k2] = u[k2];
     }
+#pragma unroll
+    for (int e = 0; e < N1; ++e) v[e] = o[e];
+  }
+}
+
+// The exchange between the stages through the line's LDS row.
+template <int N1, int N2, bool WAVE>
+__device__ __forceinline__ void exchange(float2 (&v)[N1], int t, float2* lbuf) {
+  if constexpr (N2 > 1) {
+    using G = LineGeom<N1, N2>;
+    constexpr int R = N1 / N2;
     line_sync<WAVE>();  // earlier readers of this line's LDS row are done
 #pragma unroll
     for (int k1 = 0; k1 < N1; ++k1) lbuf[k1 * G::ROW + t] = v[k1];
     line_sync<WAVE>();
-    constexpr int R = N1 / N2;
 #pragma unroll
-    for (int a = 0; a < R; ++a) {
-      float2 u[N2];
-      const int k1 = t + N2 * a;
+    for (int a = 0; a < R; ++a)
 #pragma unroll
-      for (int n2 = 0; n2 < N2; ++n2) u[n2] = lbuf[k1 * G::ROW + n2];
-      dft<N2, INV>(u, K);
-#pragma unroll
-      for (int k2 = 0; k2 < N2; ++k2) v[a + R * k2] = u[k2];
-    }
+      for (int n2 = 0; n2 < N2; ++n2) v[a * N2 + n2] = lbuf[(t + N2 * a) * G::ROW + n2];
+    // the reads are issued here: what follows in the source runs while they
+    // are under way
+    __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// One whole transform.
+template <int N1, int N2, bool INV, bool WAVE, bool REG>
+__device__ __forceinline__ void line_fft(float2 (&v)[N1], const LaneTwiddles<N1, N2, REG>& tw, int t, float2* lbuf,
+                                         const DftConsts& K) {
+  line_stage1<N1, N2, INV>(v, tw, K);
+  exchange<N1, N2, WAVE>(v, t, lbuf);
+  line_stage2<N1, N2, INV>(v, K);
+}
+
+// FFT . P . IFFT along the line for the NF fields a lane holds (prop: P of
+// field j at prop + j N; CONJ: conj(P)).  The fields' transforms are
+// interleaved: while one field's exchange is under way (its LDS reads take
+// some hundred cycles, and a SIMD holds three waves at most here) the lane
+// works on the registers of another.  With the twiddles in registers this
+// took the fused x / tau passes of 256^3 points and three fields from 196 /
+// 219 us to 181 / 200 us, and those of 64^3 points and two fields from 8.7 /
+// 9.1 us to 7.9 / 8.3 us (one field after another, twiddles from LDS).
+template <int N1, int N2, int NF, bool WAVE, bool CONJ, bool REG>
+__device__ __forceinline__ void line_trip(float2 (&v)[NF][N1], const LaneTwiddles<N1, N2, REG>& tw, int t,
+                                          float2* lbuf, const float2* prop, const DftConsts& K) {
+  auto middle = [&](int j) {   // the forward transform's end, P, the inverse one's beginning
+    line_stage2<N1, N2, false>(v[j], K);
+#pragma unroll
+    for (int e = 0; e < N1; ++e) {
+      const float2 p = prop[j * N1 * N2 + t + N2 * e];
+      v[j][e] = CONJ ? cmulc(v[j][e], p) : cmul(v[j][e], p);
+    }
+    line_stage1<N1, N2, true>(v[j], tw, K);
+  };
+  if constexpr (N2 == 1) {   // nothing to wait for: one field after another
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+      line_stage1<N1, N2, false>(v[j], tw, K);
+      middle(j);
+      if (j + 1 < NF) {   // (the next field begins behind this one's results: no instructions)
+#pragma unroll
+        for (int e = 0; e < N1; ++e)
+          asm volatile("" : "+v"(v[j][e].x), "+v"(v[j][e].y), "+v"(v[j + 1][e].x), "+v"(v[j + 1][e].y));
+      }
+    }
+    return;
+  }
+  // (the schedule barriers keep the pieces apart: their temporaries would
+  // not all fit beside the fields' registers)
+  line_stage1<N1, N2, false>(v[0], tw, K);
+#pragma unroll
+  for (int j = 0; j < NF; ++j) {
+    exchange<N1, N2, WAVE>(v[j], t, lbuf);
+    if (j + 1 < NF) line_stage1<N1, N2, false>(v[j + 1], tw, K);
+    __builtin_amdgcn_sched_barrier(0);
+    if (j > 0) middle(j - 1);
+  }
+#pragma unroll
+  for (int j = 0; j < NF; ++j) {
+    if (j == 0 && NF == 1) middle(0);
+    exchange<N1, N2, WAVE>(v[j], t, lbuf);
+    if (j == 0 && NF > 1) middle(NF - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (j > 0) line_stage2<N1, N2, true>(v[j - 1], K);
+  }
+  line_stage2<N1, N2, true>(v[NF - 1], K);
 }
 
 // ---------------------------------------------------------------------------
@@ -294,28 +405,6 @@ __device__ inline void store_slot(__amdgpu_buffer_rsrc_t r, unsigned lane_bytes,
   __builtin_amdgcn_raw_buffer_store_b64(w, r, lane_bytes, slot_bytes, NT ? 2 : 0);
 }
 
-template <bool NT>
-__device__ inline float2 load_field(const float2* base, unsigned idx) {
-  if constexpr (NT) {
-    const f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(base) + idx);
-    return make_float2(v.x, v.y);
-  } else {
-    return base[idx];
-  }
-}
-
-template <bool NT>
-__device__ inline void store_field(float2* base, unsigned idx, float2 v) {
-  if constexpr (NT) {
-    f32x2 w;
-    w.x = v.x;
-    w.y = v.y;
-    __builtin_nontemporal_store(w, reinterpret_cast<f32x2*>(base) + idx);
-  } else {
-    base[idx] = v;
-  }
-}
-
 // Transverse phase factors of slot e at the half-step's three stage
 // positions: read per slot along x, the column's values along tau.
 template <int AX, int N2>
@@ -337,13 +426,130 @@ __device__ __forceinline__ void map_factors(const float2* map, unsigned plane, u
 //   Y: line = (x, tau), element stride nx, lanes x-fastest (coalesced rows)
 //   T: line = (x, y),   element stride nx*ny, lanes (x,y)-fastest
 // NF is the number of fields held by one thread (Y: 1, one field per block).
-// FULL: every line of every block exists (no bounds masks).
 // ---------------------------------------------------------------------------
+// Where a line's elements lie.  Lines past the last one (the last block's)
+// are given the last line's addresses: they read and compute like it and
+// store nothing (valid is false).
+struct LineAddr {
+  unsigned base, estride;
+  unsigned lidx;   // long tau axis: a (b passes) or k_b (a pass) of the line
+  bool valid;
+};
+
+template <int AX, int N, class Args>
+__device__ __forceinline__ LineAddr line_addr(const Args& args, unsigned line) {
+  const unsigned nx = args.nx, plane = unsigned(args.nx) * unsigned(args.ny);
+  LineAddr a{0, 1, 0, true};
+  if constexpr (AX == AX_X) {
+    const unsigned lines = unsigned(args.ny) * unsigned(args.nt);
+    a.valid = line < lines;
+    a.base = min(line, lines - 1u) * nx;
+  } else if constexpr (AX == AX_Y) {
+    // lines (x, tau) numbered x-fastest, so that a block's lines are
+    // consecutive x (coalesced rows) and only the last block can be partial
+    const unsigned lines = nx * unsigned(args.nt);
+    a.valid = line < lines;
+    line = min(line, lines - 1u);
+    a.base = line % nx + plane * (line / nx);
+    a.estride = nx;
+  } else if constexpr (long_tau_kind(AX)) {
+    // lines (column, a) of the b transforms or (column, k_b) of the a
+    // transforms, column-fastest: a block's lines are consecutive columns
+    const unsigned nsub = unsigned(args.nt) / unsigned(N);     // A (b passes) or B (a pass)
+    a.valid = line < plane * nsub;
+    line = min(line, plane * nsub - 1u);
+    const unsigned col = line % plane;
+    a.lidx = line / plane;
+    if constexpr (AX == AX_TB) {
+      a.base = col + plane * unsigned(N) * a.lidx;   // elements a at tau = a + A k_b
+      a.estride = plane;
+    } else {
+      a.base = col + plane * a.lidx;                 // elements b at tau = a + A b
+      a.estride = plane * nsub;
+    }
+  } else {
+    a.valid = line < plane;
+    a.base = min(line, plane - 1u);
+    a.estride = plane;
+  }
+  return a;
+}
+
+// This step's twiddles and the block's propagators go through LDS, the
+// fields straight to registers.  All table loads are issued first and
+// together (begin), then the field loads; only then are the table values
+// waited for (loads return in order) and written to LDS (end), with the
+// field loads still in flight: one memory latency instead of one per table
+// and loop trip, and no block that waits for its tables with no field load
+// outstanding (long tau passes of 128 x 128 x 1024: 11 % less time for the
+// whole step).
+template <int N, int NF, int BLOCK, bool FUSE>
+struct StageTables {
+  static constexpr int TT = (N + BLOCK - 1) / BLOCK;        // table entries per thread
+  static constexpr int TP = (NF * N + BLOCK - 1) / BLOCK;
+  float2 tw[TT], prop[TP], tw2[FUSE ? TT : 1], prop2[FUSE ? TP : 1];
+
+  template <class Args>
+  __device__ __forceinline__ void begin(const Args& args, int field0, int tid) {
+#pragma unroll
+    for (int q = 0; q < TT; ++q) {
+      const int i = min(tid + q * BLOCK, N - 1);
+      tw[q] = args.tw[i];
+      if constexpr (FUSE) tw2[q] = args.tw2[i];
+    }
+#pragma unroll
+    for (int q = 0; q < TP; ++q) {
+      const int k = min(tid + q * BLOCK, NF * N - 1);
+      const int i = (field0 + k / N) * args.field_stride + args.axis_off + k % N;
+      prop[q] = args.prop[i];
+      if constexpr (FUSE) prop2[q] = args.prop2[i];
+    }
+  }
+
+  // conj: lay the conjugate propagators down
+  __device__ __forceinline__ void end(bool conj, int tid, float2* s_tw, float2* s_prop, float2* s_tw2,
+                                      float2* s_prop2) {
+#pragma unroll
+    for (int q = 0; q < TT; ++q) {
+      const int i = tid + q * BLOCK;
+      if (N % BLOCK == 0 || i < N) {
+        s_tw[i] = tw[q];
+        if constexpr (FUSE) s_tw2[i] = tw2[q];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < TP; ++q) {
+      const int i = tid + q * BLOCK;
+      if (conj) prop[q].y = -prop[q].y;
+      if ((NF * N) % BLOCK == 0 || i < NF * N) {
+        s_prop[i] = prop[q];
+        if constexpr (FUSE) s_prop2[i] = prop2[q];
+      }
+    }
+  }
+};
+
+// RK4 coefficients of a half-step: the same for every thread, read before
+// any store and kept in scalar registers.
+template <int NF>
+__device__ __forceinline__ void load_coefficients(const float2* nl, float2 (&co)[NF][kNlCoef]) {
+#pragma unroll
+  for (int j = 0; j < NF; ++j)
+#pragma unroll
+    for (int c = 0; c < kNlCoef; ++c) co[j][c] = wave_uniform(nl[j * kNlCoef + c]);
+}
+
+// Whether a lane's twiddles stay in registers: where its values leave room.
+template <int N1, int NF, int BLOCK>
+constexpr bool twiddle_registers() {
+  return BLOCK > kBlock ? N1 <= 16 : N1 * NF <= 72;
+}
+
 // bx: tile index along the launch's x dimension; field0: first field
 // handled (y pass: the block's field); next: a fused pass also applies the
 // next step's transform (false: the problem's last step, which ends on its
 // own second half-step).
-template <int N1, int N2, int AX, int NF, int NL, bool FULL, int BLOCK = kBlock>
+template <int N1, int N2, int AX, int NF, int NL, int BLOCK = kBlock>
 __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx, int field0,
                                                bool next = true) {
   using G = LineGeom<N1, N2, BLOCK>;
@@ -353,6 +559,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   constexpr bool NT = (AX == AX_X) ? bool(BRAHMS_NT_X) : bool(BRAHMS_NT_YT);
   constexpr bool LONG = long_tau_kind(AX);
   constexpr bool FUSE = (NL & NL_FUSE) != 0;   // and the next step's transform
+  constexpr bool REG = twiddle_registers<N1, NF, BLOCK>();
   // x lines: a line's N2 lanes are consecutive threads, within one wavefront
   constexpr bool WL = AX == AX_X && N2 <= 64 && 64 % N2 == 0;
   static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)),
@@ -369,109 +576,27 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   __shared__ float2 s_long[LONG ? kMaxLongT : 1];
 
   const int tid = threadIdx.x;
-  // RK4 coefficients of the half-step: the same for every thread, read
-  // before any store and kept in scalar registers
   float2 co[NF][kNlCoef];
-  if constexpr (NLM != NL_NONE) {
-#pragma unroll
-    for (int j = 0; j < NF; ++j)
-#pragma unroll
-      for (int c = 0; c < kNlCoef; ++c)
-        co[j][c] = wave_uniform(((NLM & NL_BEFORE) != 0 ? args.nl : args.nl2)[j * kNlCoef + c]);
-  }
-  // this step's twiddles and this block's propagators, staged once
-  if constexpr (LONG) {
-    // args.tw is the nt-point row exp(-2 pi i m / nt); the line transforms
-    // of length N take every (nt / N)-th entry
-    const int nt = args.nt;
-    const int stride = nt / N;
-    for (int i = tid; i < N; i += BLOCK) s_tw[i] = args.tw[i * stride];
-    if constexpr (AX == AX_TB) {
-      const float2* pr = args.prop + field0 * args.field_stride + args.axis_off;
-      for (int i = tid; i < nt; i += BLOCK) {
-        float2 pv = pr[i];
-        if (args.conj) pv.y = -pv.y;
-        s_long[i] = pv;
-      }
-    } else {
-      for (int i = tid; i < nt; i += BLOCK) s_long[i] = args.tw[i];
-    }
-  } else {
-    for (int i = tid; i < N; i += BLOCK) s_tw[i] = args.tw[i];
-    for (int i = tid; i < NF * N; i += BLOCK) {
-      float2 pv = args.prop[(field0 + i / N) * args.field_stride + args.axis_off + i % N];
-      if (args.conj) pv.y = -pv.y;
-      s_prop[i] = pv;
-    }
-    if constexpr (FUSE) {
-      for (int i = tid; i < N; i += BLOCK) s_tw2[i] = args.tw2[i];
-      for (int i = tid; i < NF * N; i += BLOCK)
-        s_prop2[i] = args.prop2[(field0 + i / N) * args.field_stride + args.axis_off + i % N];
-    }
-  }
+  if constexpr (NLM != NL_NONE) load_coefficients<NF>((NLM & NL_BEFORE) != 0 ? args.nl : args.nl2, co);
 
-  int t, li;
-  unsigned base, estride;
-  unsigned lidx = 0;     // long tau axis: a (b passes) or k_b (a pass) of the line
-  bool valid = true;
+  const int t = AX == AX_X ? tid % N2 : tid / G::LPB;
+  const int li = AX == AX_X ? tid / N2 : tid % G::LPB;
+  // tau pass: tiles of consecutive (x, y) columns; concurrently running
+  // blocks are spread over the whole plane so that their strided rows fall
+  // into many memory channels rather than one narrow address window
+  if constexpr (AX == AX_T) bx = unsigned((unsigned long long)bx * args.tile_mul % args.tiles);
+  const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
+  const bool valid = la.valid;
+  const unsigned lidx = la.lidx;
   const float2* fin[NF];
   float2* fout[NF];
-  if constexpr (AX == AX_X) {
-    t = tid % N2;
-    li = tid / N2;
-    const unsigned line = bx * unsigned(G::LPB) + li;
-    if constexpr (!FULL) valid = line < unsigned(args.ny) * unsigned(args.nt);
-    base = line * unsigned(args.nx);
-    estride = 1;
-  } else if constexpr (AX == AX_Y) {
-    // lines (x, tau) numbered x-fastest, so that a block's LPB lines are
-    // consecutive x (coalesced rows) and only the last block can be partial
-    li = tid % G::LPB;
-    t = tid / G::LPB;
-    const unsigned line = bx * unsigned(G::LPB) + li;
-    if constexpr (!FULL) valid = line < unsigned(args.nx) * unsigned(args.nt);
-    const unsigned xx = line % unsigned(args.nx);
-    const unsigned tt = line / unsigned(args.nx);
-    base = xx + unsigned(args.nx) * unsigned(args.ny) * tt;
-    estride = args.nx;
-  } else if constexpr (LONG) {
-    // lines (column, a) of the b transforms or (column, k_b) of the a
-    // transforms, column-fastest: a block's lines are consecutive columns
-    li = tid % G::LPB;
-    t = tid / G::LPB;
-    const unsigned plane_xy = unsigned(args.nx) * unsigned(args.ny);
-    const unsigned nsub = unsigned(args.nt) / unsigned(N);     // A (b passes) or B (a pass)
-    const unsigned line = bx * unsigned(G::LPB) + li;
-    if constexpr (!FULL) valid = line < plane_xy * nsub;
-    const unsigned col = line % plane_xy;
-    // the other index: a (b passes) or k_b (a pass); clamped on padding lines
-    lidx = min(line / plane_xy, nsub - 1u);
-    if constexpr (AX == AX_TB) {
-      base = col + plane_xy * unsigned(N) * lidx;   // elements a at tau = a + A k_b
-      estride = plane_xy;
-    } else {
-      base = col + plane_xy * lidx;                 // elements b at tau = a + A b
-      estride = plane_xy * nsub;
-    }
-  } else {
-    li = tid % G::LPB;
-    t = tid / G::LPB;
-    // tiles of consecutive (x, y) columns; concurrently running blocks are
-    // spread over the whole plane so that their strided rows fall into many
-    // memory channels rather than one narrow address window
-    const unsigned tile = unsigned((unsigned long long)bx * args.tile_mul % args.tiles);
-    const unsigned q = tile * unsigned(G::LPB) + li;
-    if constexpr (!FULL) valid = q < unsigned(args.nx) * unsigned(args.ny);
-    base = q;
-    estride = unsigned(args.nx) * unsigned(args.ny);
-  }
 #pragma unroll
   for (int j = 0; j < NF; ++j) {
     fin[j] = args.f[field0 + j];
     fout[j] = args.fo[field0 + j];
   }
-  const unsigned idx0 = base + unsigned(t) * estride;
-  const unsigned estep = unsigned(N2) * estride;
+  const unsigned idx0 = la.base + unsigned(t) * la.estride;
+  const unsigned estep = unsigned(N2) * la.estride;
   // transverse-map index of slot 0 (x pass: slot e adds N2 e; tau pass: the
   // same column for every slot, so its three factors are read once here)
   unsigned plane = 0, xy0 = 0;
@@ -498,13 +623,45 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
     rout[j] = field_rsrc(fout[j], field_bytes);
   }
   float2 v[NF][N1];
+  auto load_fields = [&]() {
 #pragma unroll
-  for (int j = 0; j < NF; ++j) {
+    for (int j = 0; j < NF; ++j) {
 #pragma unroll
-    for (int e = 0; e < N1; ++e)
-      v[j][e] = valid ? load_slot<NT>(rin[j], lane_bytes, unsigned(e) * slot_bytes) : make_float2(0.f, 0.f);
+      for (int e = 0; e < N1; ++e) v[j][e] = load_slot<NT>(rin[j], lane_bytes, unsigned(e) * slot_bytes);
+    }
+  };
+  if constexpr (LONG) {
+    // args.tw is the nt-point row exp(-2 pi i m / nt); the line transforms
+    // of length N take every (nt / N)-th entry
+    static_assert(N <= BLOCK, "one twiddle per thread");
+    const int nt = args.nt;
+    const float2* whole = AX == AX_TB ? args.prop + field0 * args.field_stride + args.axis_off : args.tw;
+    const float2 w_tw = args.tw[min(tid, N - 1) * (nt / N)];
+    constexpr int U = 2;   // (nt is a multiple of 2 BLOCK)
+    float2 w_long[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) w_long[q] = whole[tid + q * BLOCK];
+    load_fields();
+    if (tid < N) s_tw[tid] = w_tw;
+    for (int i = tid;; i += U * BLOCK) {
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (AX == AX_TB && args.conj) w_long[q].y = -w_long[q].y;
+        s_long[i + q * BLOCK] = w_long[q];
+      }
+      if (i + U * BLOCK >= nt) break;
+#pragma unroll
+      for (int q = 0; q < U; ++q) w_long[q] = whole[i + (U + q) * BLOCK];
+    }
+  } else {
+    StageTables<N, NF, BLOCK, FUSE> st;
+    st.begin(args, field0, tid);
+    load_fields();
+    st.end(args.conj != 0, tid, s_tw, s_prop, s_tw2, s_prop2);
   }
   __syncthreads();  // s_tw, s_prop staged
+  LaneTwiddles<N1, N2, REG> tw;
+  tw.init(s_tw, t);
 
   if constexpr ((NLM & NL_BEFORE) != 0) {
 #pragma unroll
@@ -525,53 +682,44 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
     }
   }
 
+  if constexpr (LONG) {
 #pragma unroll
-  for (int j = 0; j < NF; ++j) {
-    if constexpr (AX == AX_TAF) {
-      // B-point transform, then exp(-2 pi i a k_b / nt) on output k_b
-      line_fft<N1, N2, false, WL>(v[j], t, lbuf, s_tw, K);
+    for (int j = 0; j < NF; ++j) {
+      if constexpr (AX == AX_TAF) {
+        // B-point transform, then exp(-2 pi i a k_b / nt) on output k_b
+        line_fft<N1, N2, false, WL>(v[j], tw, t, lbuf, K);
 #pragma unroll
-      for (int e = 0; e < N1; ++e)
-        v[j][e] = cmul(v[j][e], s_long[(lidx * unsigned(t + N2 * e)) & unsigned(args.nt - 1)]);
-    } else if constexpr (AX == AX_TAI) {
-      // conjugate twiddle, then the inverse B-point transform
+        for (int e = 0; e < N1; ++e)
+          v[j][e] = cmul(v[j][e], s_long[(lidx * unsigned(t + N2 * e)) & unsigned(args.nt - 1)]);
+      } else if constexpr (AX == AX_TAI) {
+        // conjugate twiddle, then the inverse B-point transform
 #pragma unroll
-      for (int e = 0; e < N1; ++e)
-        v[j][e] = cmulc(v[j][e], s_long[(lidx * unsigned(t + N2 * e)) & unsigned(args.nt - 1)]);
-      line_fft<N1, N2, true, WL>(v[j], t, lbuf, s_tw, K);
-    } else if constexpr (AX == AX_TB) {
-      // A-point transform over a gives frequency k = k_b + B k_a in slot k_a
-      line_fft<N1, N2, false, WL>(v[j], t, lbuf, s_tw, K);
-      const unsigned nb = unsigned(args.nt) / unsigned(N);
+        for (int e = 0; e < N1; ++e)
+          v[j][e] = cmulc(v[j][e], s_long[(lidx * unsigned(t + N2 * e)) & unsigned(args.nt - 1)]);
+        line_fft<N1, N2, true, WL>(v[j], tw, t, lbuf, K);
+      } else {
+        // A-point transform over a gives frequency k = k_b + B k_a in slot k_a
+        line_fft<N1, N2, false, WL>(v[j], tw, t, lbuf, K);
+        const unsigned nb = unsigned(args.nt) / unsigned(N);
 #pragma unroll
-      for (int e = 0; e < N1; ++e) v[j][e] = cmul(v[j][e], s_long[lidx + nb * unsigned(t + N2 * e)]);
-      line_fft<N1, N2, true, WL>(v[j], t, lbuf, s_tw, K);
-    } else {
-      line_fft<N1, N2, false, WL>(v[j], t, lbuf, s_tw, K);
-#pragma unroll
-      for (int e = 0; e < N1; ++e) v[j][e] = cmul(v[j][e], s_prop[j * N + t + N2 * e]);
-      line_fft<N1, N2, true, WL>(v[j], t, lbuf, s_tw, K);
-    }
-    if constexpr ((NLM & NL_AFTER) == 0) {
-      if (valid) {
-#pragma unroll
-        for (int e = 0; e < N1; ++e) store_slot<NT>(rout[j], lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
+        for (int e = 0; e < N1; ++e) v[j][e] = cmul(v[j][e], s_long[lidx + nb * unsigned(t + N2 * e)]);
+        line_fft<N1, N2, true, WL>(v[j], tw, t, lbuf, K);
       }
     }
+  } else {
+    line_trip<N1, N2, NF, WL, false>(v, tw, t, lbuf, s_prop, K);
   }
 
   if constexpr ((NLM & NL_AFTER) != 0) {
-    if constexpr (NLM == NL_BOTH) {
+    if constexpr (NLM == NL_BOTH) load_coefficients<NF>(args.nl2, co);
+    // (only unfused steps are asked for their values before the half-step)
+    if (!FUSE && args.pre[0] != nullptr && valid) {
 #pragma unroll
-      for (int j = 0; j < NF; ++j)
+      for (int j = 0; j < NF; ++j) {
+        const __amdgpu_buffer_rsrc_t rp = field_rsrc(args.pre[j], field_bytes);
 #pragma unroll
-        for (int c = 0; c < kNlCoef; ++c) co[j][c] = wave_uniform(args.nl2[j * kNlCoef + c]);
-    }
-    if (args.pre[0] != nullptr && valid) {
-#pragma unroll
-      for (int j = 0; j < NF; ++j)
-#pragma unroll
-        for (int e = 0; e < N1; ++e) store_field<NT>(args.pre[j], idx0 + unsigned(e) * estep, v[j][e]);
+        for (int e = 0; e < N1; ++e) store_slot<NT>(rp, lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
+      }
     }
 #pragma unroll
     for (int e = 0; e < N1; ++e) {
@@ -579,8 +727,13 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
 #pragma unroll
       for (int j = 0; j < NF; ++j) y[j] = v[j][e];
       // (after the transforms a schedule barrier between points keeps
-      // fewer registers live than the link above)
-      __builtin_amdgcn_sched_barrier(0);
+      // fewer registers live than the link above, where exchanges follow that
+      // hold the points' arithmetic in place)
+      if constexpr (FUSE && N2 == 1) {
+        if (e > 0) point_link<NF>(y, v, e - 1);
+      } else {
+        __builtin_amdgcn_sched_barrier(0);
+      }
       if constexpr (MAP) {
         float2 w[3];
         map_factors<AX, N2>(args.map, plane, xy0, e, wt, w);
@@ -593,22 +746,156 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
     }
     if constexpr (FUSE) if (next) {
       // the next step's first transform along this axis
+      __builtin_amdgcn_sched_barrier(0);
       const DftConsts K2 = *args.consts2;
-#pragma unroll
-      for (int j = 0; j < NF; ++j) {
-        line_fft<N1, N2, false, WL>(v[j], t, lbuf, s_tw2, K2);
-#pragma unroll
-        for (int e = 0; e < N1; ++e) v[j][e] = cmul(v[j][e], s_prop2[j * N + t + N2 * e]);
-        line_fft<N1, N2, true, WL>(v[j], t, lbuf, s_tw2, K2);
-      }
-    }
-    if (valid) {
-#pragma unroll
-      for (int j = 0; j < NF; ++j)
-#pragma unroll
-        for (int e = 0; e < N1; ++e) store_slot<NT>(rout[j], lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
+      LaneTwiddles<N1, N2, REG> tw2;
+      tw2.init(s_tw2, t);
+      line_trip<N1, N2, NF, WL, false>(v, tw2, t, lbuf, s_prop2, K2);
     }
   }
+  if (valid) {
+#pragma unroll
+    for (int j = 0; j < NF; ++j)
+#pragma unroll
+      for (int e = 0; e < N1; ++e) store_slot<NT>(rout[j], lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The pass with one field per thread: NF groups of T threads, group f with
+// field f's values of the block's T / N2 lines, each group transforming its
+// field; for the RK4 step the groups lay their values down in LDS, every
+// thread takes the points e = f, f + NF, ... of its place in the line with
+// all their fields, and lays the results back.  The arithmetic of every value
+// is that of axis_pass_body, so the two give the same bits and a launch may
+// take either.  It is for launches that leave SIMDs with less than two waves
+// (narrow_launch): their time is the serial chain of one wave, and here a
+// wave's chain is 1 / NF as long and there are NF times as many waves.
+// ---------------------------------------------------------------------------
+template <int N1, int N2, int AX, int NF, int NL, int T>
+__device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsigned bx, bool next = true) {
+  using G = LineGeom<N1, N2, T>;
+  constexpr int N = G::N, BLOCK = NF * T;
+  constexpr int NLM = NL & 3;
+  constexpr bool MAP = (NL & NL_MAP) != 0;
+  constexpr bool NT = (AX == AX_X) ? bool(BRAHMS_NT_X) : bool(BRAHMS_NT_YT);
+  constexpr bool FUSE = (NL & NL_FUSE) != 0;
+  constexpr bool WL = AX == AX_X && T == 64 && N2 <= 64 && 64 % N2 == 0;
+  static_assert(NLM != NL_NONE && !long_tau_kind(AX) && T % 64 == 0, "a pass with an RK4 step on one line axis");
+  static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)), "as in axis_pass_body");
+  // a group's LDS: its lines' exchange rows, or its values around the RK4 step
+  constexpr int XS = N2 > 1 ? G::LDS_ELEMS : N1 * T;
+  static_assert(XS >= N1 * T, "the exchange rows hold the group's values");
+  __shared__ float2 lds[NF * XS];
+  __shared__ float2 s_tw[N], s_prop[NF * N], s_tw2[FUSE ? N : 1], s_prop2[FUSE ? NF * N : 1];
+
+  const int tid = threadIdx.x;
+  const int f = __builtin_amdgcn_readfirstlane(tid / T);   // (T is a multiple of the wave)
+  const int g = tid % T;
+  float2 co[NF][kNlCoef];
+  load_coefficients<NF>((NLM & NL_BEFORE) != 0 ? args.nl : args.nl2, co);
+  const int t = AX == AX_X ? g % N2 : g / G::LPB;
+  const int li = AX == AX_X ? g / N2 : g % G::LPB;
+  const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
+  const unsigned idx0 = la.base + unsigned(t) * la.estride;
+  const unsigned estep = unsigned(N2) * la.estride;
+  const unsigned field_bytes = unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) * 8u;
+  const unsigned lane_bytes = idx0 * 8u, slot_bytes = estep * 8u;
+  const __amdgpu_buffer_rsrc_t rin = field_rsrc(args.f[f], field_bytes), rout = field_rsrc(args.fo[f], field_bytes);
+  const DftConsts K = *args.consts;
+  float2* mine = lds + f * XS;
+  float2* lbuf = (N2 > 1) ? mine + li * G::LSTRIDE : mine;
+
+  float2 v[N1];
+  {
+    StageTables<N, NF, BLOCK, FUSE> st;
+    st.begin(args, 0, tid);
+#pragma unroll
+    for (int e = 0; e < N1; ++e) v[e] = load_slot<NT>(rin, lane_bytes, unsigned(e) * slot_bytes);
+    st.end(false, tid, s_tw, s_prop, s_tw2, s_prop2);
+  }
+  // transverse phase factors of this thread's points
+  constexpr int P = (N1 + NF - 1) / NF;
+  float2 wm[MAP ? P : 1][3];
+  if constexpr (MAP) {
+    const unsigned plane = unsigned(args.nx) * unsigned(args.ny);
+    const unsigned xy0 = idx0 % plane;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const unsigned xy = xy0 + (AX == AX_T ? 0u : unsigned(N2 * min(f + NF * k, N1 - 1)));
+#pragma unroll
+      for (int s = 0; s < 3; ++s) wm[k][s] = (AX == AX_T && k > 0) ? wm[0][s] : args.map[s * plane + xy];
+    }
+  }
+  __syncthreads();  // s_tw, s_prop staged
+  LaneTwiddles<N1, N2, true> tw;
+  tw.init(s_tw, t);
+
+  auto rk4 = [&]() {
+    line_sync<WL>();   // this group's exchange rows are free
+#pragma unroll
+    for (int e = 0; e < N1; ++e) mine[e * T + g] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const int e = f + NF * k;
+      if (N1 % NF == 0 || e < N1) {
+        float2 y[NF];
+#pragma unroll
+        for (int j = 0; j < NF; ++j) y[j] = lds[j * XS + e * T + g];
+        if constexpr (MAP) rk4_point<NF, true>(y, co, wm[k]);
+        else rk4_point<NF>(y, co);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = y[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < N1; ++e) v[e] = mine[e * T + g];
+  };
+  float2 (&v1)[1][N1] = reinterpret_cast<float2 (&)[1][N1]>(v);
+
+  if constexpr ((NLM & NL_BEFORE) != 0) rk4();
+  line_trip<N1, N2, 1, WL, false>(v1, tw, t, lbuf, s_prop + f * N, K);
+  if constexpr ((NLM & NL_AFTER) != 0) {
+    if constexpr (NLM == NL_BOTH) load_coefficients<NF>(args.nl2, co);
+    if (!FUSE && args.pre[0] != nullptr && la.valid) {
+      const __amdgpu_buffer_rsrc_t rp = field_rsrc(args.pre[f], field_bytes);
+#pragma unroll
+      for (int e = 0; e < N1; ++e) store_slot<NT>(rp, lane_bytes, unsigned(e) * slot_bytes, v[e]);
+    }
+    rk4();
+    if constexpr (FUSE) if (next) {
+      const DftConsts K2 = *args.consts2;
+      tw.init(s_tw2, t);
+      line_trip<N1, N2, 1, WL, false>(v1, tw, t, lbuf, s_prop2 + f * N, K2);
+    }
+  }
+  if (la.valid) {
+#pragma unroll
+    for (int e = 0; e < N1; ++e) store_slot<NT>(rout, lane_bytes, unsigned(e) * slot_bytes, v[e]);
+  }
+}
+
+// Threads per field group of the split pass: one wave on x (its lines are
+// contiguous and exchange within the wave); on y and tau as many as give row
+// segments of 16 lines (128 B): 64^3 points and two fields, tau: 6.1 us with
+// 16 lines, 7.8 us with 8.
+__host__ __device__ constexpr int split_threads(int n2, int ax) {
+  return ax == AX_X || 16 * n2 < 64 ? 64 : (16 * n2 > 256 ? 256 : 16 * n2);
+}
+
+// Whether a pass over `lines` lines of n2 lanes takes one field per thread:
+// when the fields-together pass would have less than two waves for each of
+// the 1024 SIMDs.  Below that a SIMD's time is the chain of its one wave
+// (which issues at most every other slot), and splitting it wins: 32^3 and
+// two fields, fused x pass: 64 waves, 4.6 against 7.3 us; 64^3: 512 waves,
+// 5.6 / 7.8; 128 x 128 x 64: 1024 waves, 13.1 / 17.3; at 2048 waves the two
+// are even (same grid, tau: 11.5 / 11.4; 128^3 and three fields, x: 32.8 /
+// 29.8) and beyond it the fields-together pass wins, having no exchange of
+// values around the RK4 step (256^3, x: 225 / 180).
+__host__ __device__ constexpr bool narrow_launch(long long lines, int n2) {
+  return lines * n2 < 2LL * 1024 * 64;
 }
 
 // Threads per block of the wide linear passes (schedule field `wide`): twice
@@ -618,9 +905,9 @@ constexpr int kWideBlock = 2 * kBlock;
 
 // Blocks per CU a pass kernel of N1 values per lane and BLOCK threads is
 // compiled for (the second argument of its launch bounds).
-template <int N1, int BLOCK>
+template <int N1, int N2, int BLOCK>
 constexpr int pass_min_blocks() {
-  return BLOCK != kBlock ? 2 : (N1 > 24 ? 1 : BRAHMS_MIN_BLOCKS);
+  return BLOCK != kBlock ? 2 : (N1 > 24 ? 1 : (N1 >= 18 ? 2 : BRAHMS_MIN_BLOCKS));
 }
 
 // Whether the wide linear passes of a split fit the LDS of one CU (160 KB):
@@ -634,19 +921,19 @@ constexpr bool wide_split() {
 
 // One pass of one problem; BLOCK threads per block (kBlock, or kWideBlock
 // for the wide linear passes of the schedule field `wide`).
-template <int N1, int N2, int AX, int NF, int NL, bool FULL, int BLOCK = kBlock>
-__global__ __launch_bounds__(BLOCK, (pass_min_blocks<N1, BLOCK>())) void axis_pass(PassArgs args) {
+template <int N1, int N2, int AX, int NF, int NL, int BLOCK = kBlock>
+__global__ __launch_bounds__(BLOCK, (pass_min_blocks<N1, N2, BLOCK>())) void axis_pass(PassArgs args) {
   // passes with one field per block take it from blockIdx.z
   constexpr bool per_field = NF == 1;
-  axis_pass_body<N1, N2, AX, NF, NL, FULL, BLOCK>(args, blockIdx.x, per_field ? int(blockIdx.z) : 0);
+  axis_pass_body<N1, N2, AX, NF, NL, BLOCK>(args, blockIdx.x, per_field ? int(blockIdx.z) : 0);
 }
 
 // One pass over a group of problems of the same shape (a batch): descs[i]
 // describes problem i at this step; passes over all fields take the problem
 // from blockIdx.y, passes with one field per block from blockIdx.z / nf.  Problems whose own step count
 // is reached (step >= nz) leave at once.
-template <int N1, int N2, int AX, int NF, int NL, bool FULL, int BLOCK = kBlock>
-__global__ __launch_bounds__(BLOCK, (pass_min_blocks<N1, BLOCK>())) void axis_pass_batched(
+template <int N1, int N2, int AX, int NF, int NL, int BLOCK = kBlock>
+__global__ __launch_bounds__(BLOCK, (pass_min_blocks<N1, N2, BLOCK>())) void axis_pass_batched(
     const PassArgs* descs, long long step, int nf) {
   // linear y and long-tau passes take one field per block: problem and field
   // from blockIdx.z
@@ -655,8 +942,22 @@ __global__ __launch_bounds__(BLOCK, (pass_min_blocks<N1, BLOCK>())) void axis_pa
   const PassArgs& a = descs[inst];
   if (step >= a.nz) return;
   // a fused pass ends the problem's last step without the next transform
-  axis_pass_body<N1, N2, AX, NF, NL, FULL, BLOCK>(a, blockIdx.x, per_field ? int(blockIdx.z % unsigned(nf)) : 0,
-                                                  step + 1 < a.nz);
+  axis_pass_body<N1, N2, AX, NF, NL, BLOCK>(a, blockIdx.x, per_field ? int(blockIdx.z % unsigned(nf)) : 0,
+                                            step + 1 < a.nz);
+}
+
+// The passes with one field per thread, of one problem and of a group.
+template <int N1, int N2, int AX, int NF, int NL>
+__global__ __launch_bounds__((NF * split_threads(N2, AX))) void axis_pass_split(PassArgs args) {
+  axis_pass_split_body<N1, N2, AX, NF, NL, split_threads(N2, AX)>(args, blockIdx.x);
+}
+
+template <int N1, int N2, int AX, int NF, int NL>
+__global__ __launch_bounds__((NF * split_threads(N2, AX))) void axis_pass_split_batched(
+    const PassArgs* descs, long long step, int nf) {
+  const PassArgs& a = descs[blockIdx.y];
+  if (step >= a.nz) return;
+  axis_pass_split_body<N1, N2, AX, NF, NL, split_threads(N2, AX)>(a, blockIdx.x, step + 1 < a.nz);
 }
 
 // ---------------------------------------------------------------------------

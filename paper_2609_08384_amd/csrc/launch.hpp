@@ -41,6 +41,13 @@ void launch_group_pass(int axis, int nl, const GroupGeom& g, hipStream_t st, con
 template <int N1, int N2, int AX>
 void launch_group_long(int nl, const GroupGeom& g, hipStream_t st, const PassArgs* d, long long step);
 
+// Blocks of an adjoint pass over `lines` lines of length n along axis.
+inline int adjoint_blocks(int axis, long lines, int n) {
+  const int n2 = kBlock / lines_per_block(n);
+  const int lpb = (narrow_launch(lines, n2) ? split_threads(n2, axis) : kBlock) / n2;
+  return int((lines + lpb - 1) / lpb);
+}
+
 // One adjoint pass (conj-propagator transforms with the RK4 half-step's VJP)
 // along x or tau (VJP_FIRST / VJP_LAST of adjoint.hpp).
 template <int N1, int N2>
