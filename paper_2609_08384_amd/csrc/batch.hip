@@ -178,7 +178,7 @@ void make_groups(brahms_batch_s& b) {
   std::map<std::tuple<int, int, int, int, int, int>, std::vector<int>> by_key;
   for (int i = 0; i < b.n; ++i) {
     const brahms_plan_s& p = *b.plans[i];
-    const brahms::detail::StepPasses sp = brahms::detail::step_passes(p, true);
+    const brahms::detail::StepPasses sp = brahms::detail::step_passes(p);
     int code = sp.n;
     for (int k = 0; k < sp.n; ++k) code = code * 8 + sp.ax[k];
     by_key[{p.nx, p.ny, p.nt, p.nf, (p.order * 8 + p.split) * 8 + p.wide, code}].push_back(i);
@@ -208,18 +208,20 @@ void make_groups(brahms_batch_s& b) {
 // Whether a group's steps run as fused step pairs: even steps take the
 // axes a, m, b of their passes, odd steps b, m, a, and each step's last
 // transform, the merged RK4 step and the next step's first transform are one
-// launch (which ends a member's last step without the next transform).
+// launch (which ends a member's last step without the next transform); so do
+// merged steps of two axes, as in plans (fusing).
 bool group_fused(const brahms_batch_s& b, const brahms_batch_s::Group& g) {
   const brahms_plan_s& p0 = *b.plans[g.members[0]];
-  return b.merge && b.fuse && !brahms::detail::long_tau(p0) &&
-         brahms::detail::step_passes(p0, true).n == 3;
+  if (!b.merge || brahms::detail::long_tau(p0)) return false;
+  const int n = brahms::detail::step_passes(p0).n;
+  return n == 2 || (b.fuse && n == 3);
 }
 
 size_t descriptor_bytes(brahms_batch_s& b) {
   size_t off = 0;
   for (auto& g : b.groups) {
     g.desc_off = off;
-    const int npass = brahms::detail::step_passes(*b.plans[g.members[0]], true).n;
+    const int npass = brahms::detail::step_passes(*b.plans[g.members[0]]).n;
     off = align_up(off + sizeof(PassArgs) * size_t(npass) * kChunk * g.members.size());
   }
   return off;
@@ -293,13 +295,14 @@ brahms_status upload_descriptors(brahms_batch_s& b) {
       const int row_stride = table_row_stride(p.nf, p.nx, p.ny, p.nt);
       const float2* rows = reinterpret_cast<const float2*>(p.ws + p.off_prop);
       const float2* nls = reinterpret_cast<const float2*>(p.ws + p.off_nl);
-      const brahms::detail::StepPasses sp = brahms::detail::step_passes(p, true);
+      const brahms::detail::StepPasses sp = brahms::detail::step_passes(p);
       const bool fused = group_fused(b, g);
+      const int end = sp.n - 1;
       for (int pass = 0; pass < sp.n; ++pass) {
         for (int s = 0; s < kChunk; ++s) {
           // fused step pairs: odd steps swap the first and last axes
           int ax = sp.ax[pass];
-          if (fused && (s & 1) && pass != 1) ax = sp.ax[2 - pass];
+          if (fused && (s & 1) && (pass == 0 || pass == end)) ax = sp.ax[end - pass];
           const int len = ax == AX_X ? p.nx : (ax == AX_Y ? p.ny : p.nt);
           PassArgs a{};
           const float2* r = rows + size_t(s) * row_stride;
@@ -324,7 +327,7 @@ brahms_status upload_descriptors(brahms_batch_s& b) {
             a.tile_mul = brahms::detail::tile_multiplier(a.tiles);
           }
           a.nz = b.nsteps[g.members[k]];  // compared with the absolute step
-          if (fused && pass == 2) {
+          if (fused && pass == end) {
             // the next step's tables along the same axis (row s + 1)
             const float2* r2 = r + row_stride;
             a.tw2 = r2 + p.nf * per_field + a.axis_off;
@@ -377,14 +380,15 @@ brahms_status enqueue_group(brahms_batch_s& b, const brahms_batch_s::Group& g, h
     const int chunks = (g.max_steps + kChunk - 1) / kChunk;
     const bool fused = group_fused(b, g);
     for (int c = 0; c < chunks; ++c) {
-      const long total = long(kTableRows) * ((g.nf + 1) * per_field + 1) + long(kTableRows) * 2 * g.nf;
+      const long total = table_threads(kTableRows, g.nf, per_field);
       const TableArgs* targs =
           reinterpret_cast<const TableArgs*>(b.ws + b.off_targs + g.targs_off) + size_t(c) * m;
       hipLaunchKernelGGL(step_tables_batched, dim3(unsigned((total + 255) / 256), m), dim3(256), 0,
                          st, targs);
       HIP_TRY(hipGetLastError());
       const int cnt = std::min(kChunk, g.max_steps - c * kChunk);
-      const brahms::detail::StepPasses sp = brahms::detail::step_passes(p0, true);
+      const brahms::detail::StepPasses sp = brahms::detail::step_passes(p0);
+      const int end = sp.n - 1;
       for (int s = 0; s < cnt; ++s) {
         const long long step = (long long)c * kChunk + s;
         for (int pass = 0; pass < sp.n; ++pass) {
@@ -392,8 +396,8 @@ brahms_status enqueue_group(brahms_batch_s& b, const brahms_batch_s::Group& g, h
           int nl = b.merge && step > 0 && pass == 0 ? (sp.nl[pass] & ~NL_BEFORE) : sp.nl[pass];
           if (fused) {
             if (pass == 0 && step > 0) continue;   // done by the previous fused pass
-            if (s & 1) ax = sp.ax[2 - pass];
-            if (pass == 2) nl = NL_AFTER | NL_FUSE;
+            if ((s & 1) && (pass == 0 || pass == end)) ax = sp.ax[end - pass];
+            if (pass == end) nl = NL_AFTER | NL_FUSE;
           }
           const PassArgs* d = reinterpret_cast<const PassArgs*>(b.ws + b.off_desc + g.desc_off) +
                               (size_t(pass) * kChunk + s) * m;

@@ -201,7 +201,7 @@ int pass_axis(const brahms_plan_s& p, int k) {
   return axes[order][k];
 }
 
-StepPasses step_passes(const brahms_plan_s& p, bool batched) {
+StepPasses step_passes(const brahms_plan_s& p) {
   StepPasses s{};
   if (long_tau(p)) {
     const int ax[5] = {AX_X, AX_Y, AX_TAF, AX_TB, AX_TAI};
@@ -224,7 +224,7 @@ StepPasses step_passes(const brahms_plan_s& p, bool batched) {
     s.nl[0] = NL_BOTH;
     return s;
   }
-  if (batched && no_map && lossless && p.nt == 1 && p.nx > 1 && p.ny > 1) {
+  if (no_map && lossless && p.nt == 1 && p.nx > 1 && p.ny > 1) {
     s.n = 2;
     const bool x_first = p.order == 0 || p.order == 2;
     s.ax[0] = x_first ? int(AX_X) : int(AX_Y);
@@ -250,7 +250,9 @@ bool merging(const brahms_plan_s& p) {
 }
 
 bool fusing(const brahms_plan_s& p) {
-  return p.fuse && merging(p) && (long_tau(p) || step_passes(p, false).n == 3);
+  if (!merging(p)) return false;
+  const int n = long_tau(p) ? 5 : step_passes(p).n;
+  return n == 2 || (p.fuse && n >= 3);
 }
 
 brahms_status refresh_tables(brahms_plan_s& p, long long n0, int count, int row0,
@@ -276,7 +278,7 @@ brahms_status refresh_tables(brahms_plan_s& p, long long n0, int count, int row0
     const brahms_field_params& f = p.fp[j];
     ta.fc[j] = FieldCoef{f.kappa, f.diffraction, f.tan_rho, f.delay, f.k2, f.k3, f.alpha};
   }
-  const long total = long(count) * ((p.nf + 1) * per_field + 1) + long(count) * 2 * p.nf;
+  const long total = table_threads(count, p.nf, per_field);
   const bool timed = p.timing && p.timed.size() < kMaxTimed;
   if (brahms_status st = timing_start(p, 3)) return st;
   hipLaunchKernelGGL(step_tables, dim3(unsigned((total + 255) / 256)), dim3(256), 0, p.stream, ta);
@@ -346,7 +348,7 @@ brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool cont
   const size_t map_row = map ? size_t(p.map_rows == 1 ? 0 : row) * 5 * p.dk_map.size() : 0;
   // the first pass carries the first RK4 half-step, the last pass the second
   // one (the axis operators commute)
-  const StepPasses sp = step_passes(p, false);
+  const StepPasses sp = step_passes(p);
   if (continued && map) return fail(BRAHMS_E_UNSUPPORTED, "merged half-steps with a map");
   for (int k = 0; k < sp.n; ++k) {
     const int ax = sp.ax[k];
@@ -372,15 +374,17 @@ brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool cont
 
 brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last, bool odd) {
   // axes a, m, b of the schedule; odd steps run them as b, m, a.  A long
-  // tau axis is the middle one (its three passes), with x and y at the ends.
+  // tau axis is the middle one (its three passes), with x and y at the ends;
+  // a step of two axes has no middle.
   const bool lt = long_tau(p);
-  int a0 = pass_axis(p, 0), b0 = pass_axis(p, 2);
+  const StepPasses sp = step_passes(p);
+  int a0 = sp.ax[0], b0 = sp.ax[sp.n - 1];
   if (lt) {
     a0 = (p.order & 1) ? int(AX_Y) : int(AX_X);
     b0 = (p.order & 1) ? int(AX_X) : int(AX_Y);
   }
-  const int mids[3] = {lt ? int(AX_TAF) : pass_axis(p, 1), int(AX_TB), int(AX_TAI)};
-  const int nmid = lt ? 3 : 1;
+  const int mids[3] = {lt ? int(AX_TAF) : sp.ax[1], int(AX_TB), int(AX_TAI)};
+  const int nmid = lt ? 3 : sp.n - 2;
   const int lead = odd ? b0 : a0, tail = odd ? a0 : b0;
   auto in_place = [&](PassArgs& a) {
     for (int j = 0; j < 3; ++j) {
@@ -774,7 +778,7 @@ brahms_status brahms_plan_set_schedule(brahms_plan plan, const brahms_schedule* 
     return fail(BRAHMS_E_INVALID_ARG, "fuse_steps must be 0 or 1");
   if (sched->fuse_steps && !sched->merge_halves)
     return fail(BRAHMS_E_INVALID_ARG, "fuse_steps needs merge_halves");
-  if (sched->fuse_steps && !detail::long_tau(*plan) && detail::step_passes(*plan, false).n != 3)
+  if (sched->fuse_steps && !detail::long_tau(*plan) && detail::step_passes(*plan).n == 1)
     return fail(BRAHMS_E_UNSUPPORTED, "fuse_steps needs an x and a y pass (not nx = ny = 1 with tau <= 256)");
   if (sched->split < 0 || sched->split > 7) return fail(BRAHMS_E_INVALID_ARG, "split must be 0 .. 7");
   if (sched->wide < 0 || sched->wide > 7) return fail(BRAHMS_E_INVALID_ARG, "wide must be 0 .. 7");

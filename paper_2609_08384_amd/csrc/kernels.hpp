@@ -542,7 +542,7 @@ __device__ __forceinline__ void load_coefficients(const float2* nl, float2 (&co)
 // Whether a lane's twiddles stay in registers: where its values leave room.
 template <int N1, int NF, int BLOCK>
 constexpr bool twiddle_registers() {
-  return BLOCK > kBlock ? N1 <= 16 : N1 * NF <= 72;
+  return BLOCK > kBlock ? N1 <= 16 : N1 * NF <= 72;   // (short blocks as kBlock)
 }
 
 // bx: tile index along the launch's x dimension; field0: first field
@@ -907,7 +907,7 @@ constexpr int kWideBlock = 2 * kBlock;
 // compiled for (the second argument of its launch bounds).
 template <int N1, int N2, int BLOCK>
 constexpr int pass_min_blocks() {
-  return BLOCK != kBlock ? 2 : (N1 > 24 ? 1 : (N1 >= 18 ? 2 : BRAHMS_MIN_BLOCKS));
+  return BLOCK > kBlock ? 2 : (N1 > 24 ? 1 : (N1 >= 18 ? 2 : BRAHMS_MIN_BLOCKS));
 }
 
 // Whether the wide linear passes of a split fit the LDS of one CU (160 KB):
@@ -966,7 +966,7 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void axis_pass_split_
 // Propagator of field j along one axis for step n (z_n = n dz):
 //   P_n(k) = s * U(z_{n+1}, k) * conj(U(z_n, k)),   U(z, k) = fl32(exp(i phi(k) z))
 // with phi the imaginary part of that axis's share of the symbol Lambda_j,
-// the phase reduced mod 2 pi in double before the sine and cosine, and s the
+// the phase reduced to a turn in double before the sine and cosine, and s the
 // 1/N normalisation (times exp(-alpha dz/2) on the tau axis).  Because U is
 // rounded at every z_n separately, the phase rounding errors of consecutive
 // steps cancel (a telescoping product) instead of accumulating coherently.
@@ -1015,10 +1015,17 @@ __host__ __device__ inline int table_row_stride(int nf, int nx, int ny, int nt) 
   return (nf + 1) * (nx + ny + nt) + int(sizeof(DftConsts) / sizeof(float2));
 }
 
-__device__ inline double reduce_2pi(double a) {
-  const double two_pi = 6.283185307179586476925286766559;
-  double r = fmod(a, two_pi);
-  return r < 0.0 ? r + two_pi : r;
+// sin and cos of a phase of any size: its part of a turn, a / (2 pi) minus the
+// nearest integer, in two-term arithmetic (the product's rounding error and
+// the rest of 1 / (2 pi) are added back after the integer is gone), then
+// sincospi.  (With fmod and sincos the table kernel of one step of 32^3 took
+// 8.2 us, most of a call's time; it is a chain of FP64 instructions.)
+__device__ inline void phase_sincos(double a, double* sn, double* cs) {
+  const double inv = 0.15915494309189534561, inv_lo = -9.8393381170937e-18;
+  const double t = a * inv;
+  const double lo = fma(a, inv_lo, fma(a, inv, -t));
+  const double r = (t - rint(t)) + lo;
+  sincospi(2.0 * r, sn, cs);
 }
 
 __device__ inline double ang_freq(int m, int n, double d) {
@@ -1028,7 +1035,7 @@ __device__ inline double ang_freq(int m, int n, double d) {
 
 __device__ inline double2 rounded_unit(double theta) {
   double s, c;
-  sincos(reduce_2pi(theta), &s, &c);
+  phase_sincos(theta, &s, &c);
   return make_double2(double(float(c)), double(float(s)));
 }
 
@@ -1137,11 +1144,14 @@ __device__ __forceinline__ void step_tables_body(const TableArgs& a, long gid) {
     return;
   }
   const long g2 = gid - nrow;
-  const long nco = long(a.count) * 2 * a.nf;
+  // RK4 coefficients: one thread each
+  const long nco = long(a.count) * 2 * a.nf * kNlCoef;
   if (g2 >= nco) return;
-  const int s = int(g2 / (2 * a.nf));
-  const int half = int((g2 / a.nf) % 2);
-  const int j = int(g2 % a.nf);
+  const int k = int(g2 % kNlCoef);
+  const long g3 = g2 / kNlCoef;
+  const int s = int(g3 / (2 * a.nf));
+  const int half = int((g3 / a.nf) % 2);
+  const int j = int(g3 % a.nf);
   const long n = table_n0(a) + s;
   double phi_n, dkn;
   if (a.dk != nullptr) {
@@ -1160,24 +1170,23 @@ __device__ __forceinline__ void step_tables_body(const TableArgs& a, long gid) {
   const bool merged = half == 1 && n < table_merge_last(a);
   const double h = merged ? a.dz : 0.5 * a.dz;
   const double kap = a.fc[j].kappa;
-  double2 c[3];  // c_j at z_a, z_a + h/2, z_a + h
-  for (int k = 0; k < 3; ++k) {
-    const double off = merged ? (0.5 + 0.5 * double(k)) * a.dz                   // z - z_n
-                              : (double(half) * 2.0 + double(k)) * 0.25 * a.dz;
-    const double ph = reduce_2pi(phi_n + dkn * off);
-    double sn, cs;
-    sincos(ph, &sn, &cs);
-    // i kappa (cos + i sigma sin) = kappa (-sigma sin + i cos)
-    c[k] = make_double2(-kap * sigma * sn, kap * cs);
-  }
-  const double w[6] = {h / 2, h / 2, h, h / 6, h / 3, h / 6};
-  const int which[6] = {0, 1, 1, 0, 1, 2};
-  float2* out = a.nl + g2 * kNlCoef;
-  for (int k = 0; k < 6; ++k) {
-    const unsigned slot = 0x50000000u + unsigned((half * a.nf + j) * kNlCoef + k) * 2u;
-    out[k] = make_float2(stochastic_round(w[k] * c[which[k]].x, entry_bits(n, slot)),
-                         stochastic_round(w[k] * c[which[k]].y, entry_bits(n, slot + 1)));
-  }
+  // weights of a1, a2, a3, b1, b2, b4 and the stage (z_a, z_a + h/2, z_a + h)
+  // of each one's c_j
+  const double w = k < 2 ? h / 2 : (k == 2 ? h : (k == 4 ? h / 3 : h / 6));
+  const int stage = k == 0 || k == 3 ? 0 : (k == 5 ? 2 : 1);
+  const double off = merged ? (0.5 + 0.5 * double(stage)) * a.dz                   // z - z_n
+                            : (double(half) * 2.0 + double(stage)) * 0.25 * a.dz;
+  double sn, cs;
+  phase_sincos(phi_n + dkn * off, &sn, &cs);
+  // i kappa (cos + i sigma sin) = kappa (-sigma sin + i cos)
+  const unsigned slot = 0x50000000u + unsigned((half * a.nf + j) * kNlCoef + k) * 2u;
+  a.nl[g2] = make_float2(stochastic_round(w * (-kap * sigma * sn), entry_bits(n, slot)),
+                         stochastic_round(w * (kap * cs), entry_bits(n, slot + 1)));
+}
+
+// Threads of a table launch over `count` steps.
+inline long table_threads(int count, int nf, int per_field) {
+  return long(count) * ((nf + 1) * per_field + 1 + 2 * nf * kNlCoef);
 }
 
 static __global__ void step_tables(TableArgs a) {
@@ -1217,7 +1226,7 @@ static __global__ void map_phase_table(MapArgs a) {
   float2* out = a.out + size_t(blockIdx.y) * 5 * a.plane;
   for (int k = 0; k < 5; ++k) {
     double sn, cs;
-    sincos(reduce_2pi(m * (psi_n + s_n * (0.25 * k) * a.dz)), &sn, &cs);
+    phase_sincos(m * (psi_n + s_n * (0.25 * k) * a.dz), &sn, &cs);
     out[k * a.plane + i] = make_float2(float(cs), float(sn));
   }
 }

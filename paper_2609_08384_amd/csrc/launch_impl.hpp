@@ -15,15 +15,24 @@ inline unsigned blocks_of(long lines, int lpb) { return unsigned((lines + lpb - 
 
 // A linear pass (one field per block) over `lines` lines along AX, with
 // kBlock or (wide, where the split has a wide form) kWideBlock threads per
-// block.
+// block, or, in launches of few waves, with as few as split_threads, which
+// spread over more CUs (two fields, 32^3: 2.8-3.1 instead of 3.3-3.6 us; 96 x
+// 96 x 64, x: 8.4 / 9.9; CW 128 x 128: 3.7-4.0 / 4.8-4.9).
 template <int N1, int N2, int AX>
-void launch_linear(bool wide, long lines, int nf, hipStream_t st, const PassArgs& a) {
+void launch_linear(bool wide, long lines, int nf, hipStream_t st, PassArgs a) {
   if constexpr (wide_split<N1>()) {
     if (wide) {
       const dim3 grid(blocks_of(lines, LineGeom<N1, N2, kWideBlock>::LPB), 1, unsigned(nf));
       hipLaunchKernelGGL((axis_pass<N1, N2, AX, 1, NL_NONE, kWideBlock>), grid, dim3(kWideBlock), 0, st, a);
       return;
     }
+  }
+  constexpr int T = split_threads(N2, AX);
+  if (T < kBlock && narrow_launch(lines * nf, N2)) {
+    a.tiles = blocks_of(lines, T / N2);   // (the tau pass's tiles are its own blocks)
+    a.tile_mul = 1;
+    hipLaunchKernelGGL((axis_pass<N1, N2, AX, 1, NL_NONE, T>), dim3(a.tiles, 1, unsigned(nf)), dim3(T), 0, st, a);
+    return;
   }
   const dim3 grid(blocks_of(lines, LineGeom<N1, N2>::LPB), 1, unsigned(nf));
   hipLaunchKernelGGL((axis_pass<N1, N2, AX, 1, NL_NONE>), grid, dim3(kBlock), 0, st, a);
@@ -166,6 +175,12 @@ void launch_group_axis(int nl, long lines, const GroupGeom& g, hipStream_t st, c
   if (nl != NL_NONE) return launch_batched_nl<N1, N2, AX>(nl, lines, g, st, d, step);
   if constexpr (AX != AX_T && wide_split<N1>()) {
     if ((g.wide >> AX) & 1) return launch_batched_linear<N1, N2, AX, kWideBlock>(lines, g, st, d, step);
+  }
+  // (a batch's linear tau passes keep the blocks of their descriptors' tiles)
+  constexpr int T = split_threads(N2, AX);
+  if constexpr (AX != AX_T && T < kBlock) {
+    if (narrow_launch((long long)lines * g.nf * g.m, N2))
+      return launch_batched_linear<N1, N2, AX, T>(lines, g, st, d, step);
   }
   launch_batched_linear<N1, N2, AX>(lines, g, st, d, step);
 }

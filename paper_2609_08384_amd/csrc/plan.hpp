@@ -139,22 +139,22 @@ brahms_status refresh_tables(brahms_plan_s& p, long long n0, int count, int row0
 // map, and not while monitor records or snapshots are due (every step they
 // look at must end on its own second half-step).
 bool merging(const brahms_plan_s& p);
-// Whether a call fuses step pairs: merging, and x and y passes at the ends
-// of a step (three passes, or a long tau axis in the middle).
+// Whether a call fuses step pairs: merging, and either asked for (three
+// passes, or a long tau axis between x and y) or a step of two axes, where it
+// leaves one pass of a step's three and costs nothing.
 bool fusing(const brahms_plan_s& p);
 // The passes of one z-step in order: axis (AX_*) and RK4 mode (NL_*) of
 // each.  Three passes in general; passes along an axis of length 1 are left
 // out when they would multiply by exactly 1 (so the result is unchanged bit
-// for bit): nx = ny = 1 takes one tau pass with both half-steps; in a batch,
-// nt = 1 with no loss and no transverse map takes x and y passes (a single
-// CW problem keeps its tau pass, whose many short lines are its parallelism);
-// a long tau axis takes five passes.
+// for bit): nx = ny = 1 takes one tau pass with both half-steps; nt = 1 with
+// no loss and no transverse map takes x and y passes; a long tau axis takes
+// five passes.
 struct StepPasses {
   int n;
   int ax[5];
   int nl[5];
 };
-StepPasses step_passes(const brahms_plan_s& p, bool batched);
+StepPasses step_passes(const brahms_plan_s& p);
 // One z-step with the tables of `row`; with continued = true the step's first
 // half-step is left out (it was merged into the previous step's second one).
 brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool continued = false);
