@@ -141,7 +141,7 @@ brahms_status adj_pass(brahms_plan_s& p, const AdjLayout& L, int set, int row, i
 // Run steps s0 .. s0+cnt-1 (table rows of the set) out of place through the
 // set's segment slots, keeping every step's input (slot i) and the input of
 // its second RK4 half-step; the last step writes `last_out` when given.
-brahms_status record_segment(brahms_plan_s& p, const AdjLayout& L, int set, int cnt,
+brahms_status record_segment(brahms_plan_s& p, const AdjLayout& L, int set, long long s0, int cnt,
                              float2* const* last_out) {
   for (int i = 0; i < cnt; ++i) {
     brahms::detail::StepIO io{};
@@ -152,7 +152,8 @@ brahms_status record_segment(brahms_plan_s& p, const AdjLayout& L, int set, int 
                       : state_field(p.adj_ws + L.seg[set], L, p, i + 1, j);
       io.pre[j] = state_field(p.adj_ws + L.pre[set], L, p, i, j);
     }
-    if (brahms_status st = brahms::detail::launch_step(p, set * kSetRows + i, io)) return st;
+    const bool odd = brahms::detail::pairing(p) && ((s0 + i) & 1) != 0;   // the axis order of brahms_step
+    if (brahms_status st = brahms::detail::launch_step(p, set * kSetRows + i, io, false, odd)) return st;
   }
   return BRAHMS_OK;
 }
@@ -169,7 +170,7 @@ brahms_status recompute_segment(brahms_plan_s& p, const AdjLayout& L, int c, int
     ck[j] = state_field(p.adj_ws + L.ckpt, L, p, c, j);
   }
   if (brahms_status st = copy_state(p, slot0, ck)) return st;
-  return record_segment(p, L, set, cnt, nullptr);
+  return record_segment(p, L, set, s0, cnt, nullptr);
 }
 
 // Reverse sweep over segment c held in a set, then its dJ/dPhi reduction.
@@ -257,7 +258,7 @@ brahms_status brahms_adjoint_forward(brahms_plan plan, int nsteps, int checkpoin
   for (int j = 0; j < p.nf; ++j) slot0[j] = state_field(p.adj_ws + L.seg[0], L, p, 0, j);
   if (brahms_status st = copy_state(p, slot0, fields)) return st;
   if (brahms_status st = brahms::detail::refresh_tables(p, p.step, cnt)) return st;
-  if (brahms_status st = record_segment(p, L, 0, cnt, fields)) return st;
+  if (brahms_status st = record_segment(p, L, 0, p.step, cnt, fields)) return st;
   p.step += cnt;
   p.adj_last_recorded = true;
   p.adj_ready = true;

@@ -212,9 +212,9 @@ void make_groups(brahms_batch_s& b) {
 // merged steps of two axes, as in plans (fusing).
 bool group_fused(const brahms_batch_s& b, const brahms_batch_s::Group& g) {
   const brahms_plan_s& p0 = *b.plans[g.members[0]];
-  if (!b.merge || brahms::detail::long_tau(p0)) return false;
+  if (brahms::detail::long_tau(p0)) return false;
   const int n = brahms::detail::step_passes(p0).n;
-  return n == 2 || (b.fuse && n == 3);
+  return n == 2 || (n == 3 && (b.fuse || !b.merge));
 }
 
 size_t descriptor_bytes(brahms_batch_s& b) {
@@ -313,6 +313,7 @@ brahms_status upload_descriptors(brahms_batch_s& b) {
           a.field_stride = per_field;
           a.nl = nls + size_t(s) * 2 * p.nf * kNlCoef;
           a.nl2 = nls + (size_t(s) * 2 + 1) * p.nf * kNlCoef;
+          if (fused && pass == end && !b.merge) a.nl = nls + size_t(s + 1) * 2 * p.nf * kNlCoef;
           a.nx = p.nx; a.ny = p.ny; a.nt = p.nt;
           for (int j = 0; j < 3; ++j) {
             a.f[j] = p.fields[j];
@@ -348,8 +349,8 @@ brahms_status upload_descriptors(brahms_batch_s& b) {
         ta.dk = p.dk.empty() ? nullptr : reinterpret_cast<const double*>(p.ws + p.off_dk);
         ta.n0 = (long long)c * kChunk;
         ta.merge_last = b.merge ? (long long)b.nsteps[g.members[k]] - 1 : -1;
-        ta.count = std::max(0, std::min(kChunk, b.nsteps[g.members[k]] - c * kChunk));
-        if (group_fused(b, g) && ta.count > 0) ta.count += 1;   // the next step's row
+        // (fused pairs: and the next step's row, where there is a next step)
+        ta.count = std::max(0, std::min(kChunk + (group_fused(b, g) ? 1 : 0), b.nsteps[g.members[k]] - c * kChunk));
         ta.nx = p.nx; ta.ny = p.ny; ta.nt = p.nt; ta.nf = p.nf;
         ta.dz = p.dz; ta.dx = p.dx; ta.dy = p.dy; ta.dt = p.dt; ta.dk_const = p.dk_const;
         for (int j = 0; j < p.nf; ++j) {
@@ -397,7 +398,7 @@ brahms_status enqueue_group(brahms_batch_s& b, const brahms_batch_s::Group& g, h
           if (fused) {
             if (pass == 0 && step > 0) continue;   // done by the previous fused pass
             if ((s & 1) && (pass == 0 || pass == end)) ax = sp.ax[end - pass];
-            if (pass == end) nl = NL_AFTER | NL_FUSE;
+            if (pass == end) nl = NL_AFTER | NL_FUSE | (b.merge ? 0 : NL_LIT);
           }
           const PassArgs* d = reinterpret_cast<const PassArgs*>(b.ws + b.off_desc + g.desc_off) +
                               (size_t(pass) * kChunk + s) * m;

@@ -187,6 +187,11 @@ long record_doubles(const brahms_plan_s& p) { return 1 + long(p.nf) * (p.nt + 1)
 namespace brahms {
 namespace detail {
 
+bool step_watched(const brahms_plan_s& p, long long step_done) {
+  if (p.mon_every > 0 && step_done % p.mon_every == 0) return true;
+  return std::find(p.snap_steps.begin(), p.snap_steps.end(), step_done) != p.snap_steps.end();
+}
+
 brahms_status after_step(brahms_plan_s& p, long long step_done) {
   if (p.mon_every > 0 && p.mon_count < p.mon_capacity && step_done % p.mon_every == 0) {
     if (brahms_status st = write_record(p, step_done, p.mon_records + long(p.mon_count) * record_doubles(p)))

@@ -341,7 +341,12 @@ brahms_status map_table(brahms_plan_s& p, long long n0, int count) {
 
 }  // namespace
 
-brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool continued) {
+bool pairing(const brahms_plan_s& p) {
+  if (long_tau(p) || merging(p)) return false;
+  return step_passes(p).n > 1;
+}
+
+brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool continued, bool odd) {
   const bool map = !p.dk_map.empty();
   if (map && p.map_rows == 1)
     if (brahms_status st = map_table(p, p.table_n0 + row, 1)) return st;
@@ -351,8 +356,8 @@ brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool cont
   const StepPasses sp = step_passes(p);
   if (continued && map) return fail(BRAHMS_E_UNSUPPORTED, "merged half-steps with a map");
   for (int k = 0; k < sp.n; ++k) {
-    const int ax = sp.ax[k];
     const bool first = k == 0, last = k == sp.n - 1;
+    const int ax = odd && (first || last) ? sp.ax[sp.n - 1 - k] : sp.ax[k];
     int nlmode = first && continued ? (sp.nl[k] & ~NL_BEFORE) : sp.nl[k];
     PassArgs a = pass_args(p, row, ax);
     if (map && nlmode != NL_NONE) {
@@ -386,6 +391,18 @@ brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last
   const int mids[3] = {lt ? int(AX_TAF) : sp.ax[1], int(AX_TB), int(AX_TAI)};
   const int nmid = lt ? 3 : sp.n - 2;
   const int lead = odd ? b0 : a0, tail = odd ? a0 : b0;
+  const bool literal = !merging(p);
+  const bool map = !p.dk_map.empty();
+  if (map && p.map_rows == 1) {
+    if (!first || !last) return fail(BRAHMS_E_UNSUPPORTED, "step pairs with one-step map tables");
+    if (brahms_status st = map_table(p, p.table_n0 + row, 1)) return st;
+  }
+  const int map_mode = map ? NL_MAP : 0;
+  auto map_factors = [&](int r, int stage) -> const float2* {   // of a row's stage offset
+    if (!map) return nullptr;
+    return reinterpret_cast<const float2*>(p.ws + p.off_maptab) +
+           (size_t(p.map_rows == 1 ? 0 : r) * 5 + size_t(stage)) * p.dk_map.size();
+  };
   auto in_place = [&](PassArgs& a) {
     for (int j = 0; j < 3; ++j) {
       a.f[j] = p.fields[j];
@@ -395,10 +412,11 @@ brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last
     a.nl2 = nl_coefficients(p, row, 1);
   };
   if (first) {
-    // the call's first step: its own first half-step, then its first axis
+    // the run's first step: its own first half-step, then its first axis
     PassArgs a = pass_args(p, row, lead);
     in_place(a);
-    if (brahms_status st = timed_dispatch(p, lead, NL_BEFORE, a)) return st;
+    a.map = map_factors(row, 0);
+    if (brahms_status st = timed_dispatch(p, lead, NL_BEFORE | map_mode, a)) return st;
   }
   for (int k = 0; k < nmid; ++k) {
     PassArgs a = pass_args(p, row, mids[k]);
@@ -407,13 +425,19 @@ brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last
   }
   PassArgs a = pass_args(p, row, tail);
   in_place(a);
-  if (last) return timed_dispatch(p, tail, NL_AFTER, a);   // its own second half-step
-  // the RK4 step of size dz from z_n + dz/2, then step n+1's first axis
+  a.map = map_factors(row, 2);
+  if (last) return timed_dispatch(p, tail, NL_AFTER | map_mode, a);   // its own second half-step
+  // the RK4 step of size dz from z_n + dz/2 (or the two half-steps), then
+  // step n+1's first axis
+  if (literal) {
+    a.nl = nl_coefficients(p, row + 1, 0);
+    a.map2 = map_factors(row + 1, 0);
+  }
   const PassArgs next = pass_args(p, row + 1, tail);
   a.tw2 = next.tw;
   a.prop2 = next.prop;
   a.consts2 = next.consts;
-  return timed_dispatch(p, tail, NL_AFTER | NL_FUSE, a);
+  return timed_dispatch(p, tail, NL_AFTER | NL_FUSE | (literal ? NL_LIT | map_mode : 0), a);
 }
 
 brahms_status launch_linear_pass(brahms_plan_s& p, int row, int axis, float2* const* fields,
@@ -479,9 +503,11 @@ brahms_status build_chunk_graph(brahms_plan_s& p) {
       for (int s = 0; s < kChunk && st == BRAHMS_OK; ++s)
         st = detail::launch_fused_step(p, s, false, false, (s & 1) != 0);
     } else {
-      const bool continued = detail::merging(p);
+      const bool continued = detail::merging(p), pairs = detail::pairing(p);
       st = detail::refresh_tables(p, 0, kChunk);
-      for (int s = 0; s < kChunk && st == BRAHMS_OK; ++s) st = detail::launch_step(p, s, io, continued);
+      for (int s = 0; s < kChunk && st == BRAHMS_OK; ++s)
+        st = pairs ? detail::launch_fused_step(p, s, s == 0, s == kChunk - 1, (s & 1) != 0)   // (from an even step)
+                   : detail::launch_step(p, s, io, continued, false);
     }
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(p.capture_stream, &g);
@@ -552,10 +578,17 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
   if (detail::fusing(p)) return run_fused(p, nsteps);
   const detail::StepIO io = plain_io(p);
   const bool merge = detail::merging(p);
+  // literal half-steps: steps alternate their axis order and run as fused
+  // pairs up to the end of a chunk of tables or a step that a monitor or
+  // snapshot looks at (the same bits wherever a run ends)
+  const bool pairs = detail::pairing(p);
+  const bool row_maps = p.dk_map.empty() || p.map_rows == kChunk;
   const long long merge_last = merge ? p.step + nsteps - 1 : -1;
   int done = 0;
   while (done < nsteps) {
-    const int count = std::min(kChunk, nsteps - done);
+    int count = std::min(kChunk, nsteps - done);
+    // a captured chunk of pairs begins with an even step
+    if (pairs && graph_chunk_ok(p) && (p.step & 1) != 0) count = 1;
     // a captured chunk has no leading half-step when merging, so the call's
     // first chunk runs eagerly
     if (count == kChunk && graph_chunk_ok(p) && !(merge && done == 0)) {
@@ -572,9 +605,17 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
     }
     if (brahms_status st = detail::refresh_tables(p, p.step, count, 0, merge_last)) return st;
     const bool watch = p.mon_every > 0 || !p.snap_steps.empty();
+    bool open = false;   // the previous step's last pass began this step
     for (int s = 0; s < count; ++s) {
-      const bool continued = merge && (done > 0 || s > 0);
-      if (brahms_status st = detail::launch_step(p, s, io, continued)) return st;
+      const long long n = p.step + s;
+      if (pairs) {
+        const bool last = s == count - 1 || !row_maps || (watch && detail::step_watched(p, n + 1));
+        if (brahms_status st = detail::launch_fused_step(p, s, !open, last, (n & 1) != 0)) return st;
+        open = !last;
+      } else {
+        const bool continued = merge && (done > 0 || s > 0);
+        if (brahms_status st = detail::launch_step(p, s, io, continued, false)) return st;
+      }
       if (watch)
         if (brahms_status st = detail::after_step(p, p.step + s + 1)) return st;
     }

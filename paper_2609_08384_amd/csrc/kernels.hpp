@@ -47,6 +47,9 @@ constexpr int NL_MAP = 4;
 // (tw2, prop2, consts2), so the last axis of step n and the first axis of
 // step n + 1 cost one read and one write of the fields.
 constexpr int NL_FUSE = 8;
+// Added to NL_AFTER | NL_FUSE (literal half-steps): the second half-step of
+// step n and the first one of step n + 1 instead of one RK4 step over both.
+constexpr int NL_LIT = 16;
 
 struct PassArgs {
   float2* f[3];          // fields read (complex64, [nt][ny][nx])
@@ -57,7 +60,8 @@ struct PassArgs {
   const float2* tw;      // this step's forward twiddles exp(-2 pi i m / N), m < N
   const float2* prop;    // this step's propagators, field j's table of this
                          // axis at prop + j * field_stride + axis_off
-  const float2* nl;      // RK4 coefficients of the step's first half-step, [nf][6]
+  const float2* nl;      // RK4 coefficients of the step's first half-step (NL_LIT:
+                         // of the next step's), [nf][6]
   const float2* nl2;     // those of its second half-step (or, when adjacent
                          // halves are merged, of one RK4 step of size dz
                          // from z_n + dz/2)
@@ -72,6 +76,7 @@ struct PassArgs {
   const float2* tw2;     // NL_FUSE: the next step's twiddles, propagators and
   const float2* prop2;   // DFT constants along the same axis
   const DftConsts* consts2;
+  const float2* map2;    // NL_LIT with NL_MAP: map of the next step's first half-step
 };
 
 // ---------------------------------------------------------------------------
@@ -564,7 +569,8 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   constexpr bool WL = AX == AX_X && N2 <= 64 && 64 % N2 == 0;
   static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)),
                 "the transverse map runs only with a half-step per pass on x or tau");
-  static_assert(!FUSE || (NLM == NL_AFTER && !MAP && !LONG),
+  constexpr bool LIT = (NL & NL_LIT) != 0;     // two half-steps between the transforms
+  static_assert(!FUSE || (NLM == NL_AFTER && !(MAP && !LIT) && !LONG),
                 "a fused step pair ends one step and begins the next on one short axis");
   __shared__ float2 lds[G::LDS_ELEMS];
   __shared__ float2 s_tw[N];
@@ -600,13 +606,16 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   // transverse-map index of slot 0 (x pass: slot e adds N2 e; tau pass: the
   // same column for every slot, so its three factors are read once here)
   unsigned plane = 0, xy0 = 0;
-  float2 wt[3];
+  float2 wt[3], wt2[3];
   if constexpr (MAP) {
     plane = unsigned(args.nx) * unsigned(args.ny);
     xy0 = idx0 % plane;
     if constexpr (AX == AX_T || LONG) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) wt[k] = args.map[k * plane + xy0];
+      for (int k = 0; k < 3; ++k) {
+        wt[k] = args.map[k * plane + xy0];
+        if constexpr (LIT) wt2[k] = args.map2[k * plane + xy0];
+      }
     }
   }
   // a line's LDS row (lines of one lane exchange nothing: no row)
@@ -721,6 +730,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
         for (int e = 0; e < N1; ++e) store_slot<NT>(rp, lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
       }
     }
+    auto half_step = [&](const float2* map, const float2* wcol) {
 #pragma unroll
     for (int e = 0; e < N1; ++e) {
       float2 y[NF];
@@ -736,7 +746,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
       }
       if constexpr (MAP) {
         float2 w[3];
-        map_factors<AX, N2>(args.map, plane, xy0, e, wt, w);
+        map_factors<AX, N2>(map, plane, xy0, e, wcol, w);
         rk4_point<NF, true>(y, co, w);
       } else {
         rk4_point<NF>(y, co);
@@ -744,7 +754,13 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
 #pragma unroll
       for (int j = 0; j < NF; ++j) v[j][e] = y[j];
     }
+    };
+    half_step(args.map, wt);
     if constexpr (FUSE) if (next) {
+      if constexpr (LIT) {
+        load_coefficients<NF>(args.nl, co);
+        half_step(args.map2, wt2);
+      }
       // the next step's first transform along this axis
       __builtin_amdgcn_sched_barrier(0);
       const DftConsts K2 = *args.consts2;
@@ -782,6 +798,7 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
   constexpr bool FUSE = (NL & NL_FUSE) != 0;
   constexpr bool WL = AX == AX_X && T == 64 && N2 <= 64 && 64 % N2 == 0;
   static_assert(NLM != NL_NONE && !long_tau_kind(AX) && T % 64 == 0, "a pass with an RK4 step on one line axis");
+  constexpr bool LIT = (NL & NL_LIT) != 0;
   static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)), "as in axis_pass_body");
   // a group's LDS: its lines' exchange rows, or its values around the RK4 step
   constexpr int XS = N2 > 1 ? G::LDS_ELEMS : N1 * T;
@@ -816,7 +833,7 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
   }
   // transverse phase factors of this thread's points
   constexpr int P = (N1 + NF - 1) / NF;
-  float2 wm[MAP ? P : 1][3];
+  float2 wm[MAP ? P : 1][3], wm2[MAP && LIT ? P : 1][3];
   if constexpr (MAP) {
     const unsigned plane = unsigned(args.nx) * unsigned(args.ny);
     const unsigned xy0 = idx0 % plane;
@@ -824,29 +841,50 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
     for (int k = 0; k < P; ++k) {
       const unsigned xy = xy0 + (AX == AX_T ? 0u : unsigned(N2 * min(f + NF * k, N1 - 1)));
 #pragma unroll
-      for (int s = 0; s < 3; ++s) wm[k][s] = (AX == AX_T && k > 0) ? wm[0][s] : args.map[s * plane + xy];
+      for (int s = 0; s < 3; ++s) {
+        wm[k][s] = (AX == AX_T && k > 0) ? wm[0][s] : args.map[s * plane + xy];
+        if constexpr (LIT) wm2[k][s] = (AX == AX_T && k > 0) ? wm2[0][s] : args.map2[s * plane + xy];
+      }
     }
   }
   __syncthreads();  // s_tw, s_prop staged
   LaneTwiddles<N1, N2, true> tw;
   tw.init(s_tw, t);
 
-  auto rk4 = [&]() {
+  // (two: NL_LIT, the next step's first half-step follows on the same points)
+  auto rk4 = [&](bool two) {
     line_sync<WL>();   // this group's exchange rows are free
 #pragma unroll
     for (int e = 0; e < N1; ++e) mine[e * T + g] = v[e];
     __syncthreads();
+    float2 y[P][NF];
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       const int e = f + NF * k;
       if (N1 % NF == 0 || e < N1) {
-        float2 y[NF];
 #pragma unroll
-        for (int j = 0; j < NF; ++j) y[j] = lds[j * XS + e * T + g];
-        if constexpr (MAP) rk4_point<NF, true>(y, co, wm[k]);
-        else rk4_point<NF>(y, co);
+        for (int j = 0; j < NF; ++j) y[k][j] = lds[j * XS + e * T + g];
+        if constexpr (MAP) rk4_point<NF, true>(y[k], co, wm[k]);
+        else rk4_point<NF>(y[k], co);
+        if constexpr (!LIT) {
 #pragma unroll
-        for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = y[j];
+          for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = y[k][j];
+        }
+      }
+    }
+    if constexpr (LIT) {
+      if (two) load_coefficients<NF>(args.nl, co);
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        const int e = f + NF * k;
+        if (N1 % NF == 0 || e < N1) {
+          if (two) {
+            if constexpr (MAP) rk4_point<NF, true>(y[k], co, wm2[k]);
+            else rk4_point<NF>(y[k], co);
+          }
+#pragma unroll
+          for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = y[k][j];
+        }
       }
     }
     __syncthreads();
@@ -855,7 +893,7 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
   };
   float2 (&v1)[1][N1] = reinterpret_cast<float2 (&)[1][N1]>(v);
 
-  if constexpr ((NLM & NL_BEFORE) != 0) rk4();
+  if constexpr ((NLM & NL_BEFORE) != 0) rk4(false);
   line_trip<N1, N2, 1, WL, false>(v1, tw, t, lbuf, s_prop + f * N, K);
   if constexpr ((NLM & NL_AFTER) != 0) {
     if constexpr (NLM == NL_BOTH) load_coefficients<NF>(args.nl2, co);
@@ -864,7 +902,7 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
 #pragma unroll
       for (int e = 0; e < N1; ++e) store_slot<NT>(rp, lane_bytes, unsigned(e) * slot_bytes, v[e]);
     }
-    rk4();
+    rk4(next);
     if constexpr (FUSE) if (next) {
       const DftConsts K2 = *args.consts2;
       tw.init(s_tw2, t);

@@ -62,6 +62,12 @@ template <int N1, int N2, int AX, int NF>
 void launch_nl_nf(int nl, long lines, hipStream_t st, const PassArgs& a) {
   if constexpr (!long_tau_kind(AX)) {
     if (nl == (NL_AFTER | NL_FUSE)) return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE>(lines, st, a);
+    if (nl == (NL_AFTER | NL_FUSE | NL_LIT))
+      return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT>(lines, st, a);
+    if constexpr (AX != AX_Y) {
+      if (nl == (NL_AFTER | NL_FUSE | NL_LIT | NL_MAP))
+        return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT | NL_MAP>(lines, st, a);
+    }
   }
   if constexpr (AX == AX_T) {
     if (nl == NL_BOTH) return launch_rk4<N1, N2, AX, NF, NL_BOTH>(lines, st, a);
@@ -154,6 +160,8 @@ void launch_batched_nl_nf(int nl, long lines, const GroupGeom& g, hipStream_t st
   if constexpr (!long_tau_kind(AX)) {
     if (nl == (NL_AFTER | NL_FUSE))
       return launch_batched_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE>(lines, g, st, d, step);
+    if (nl == (NL_AFTER | NL_FUSE | NL_LIT))
+      return launch_batched_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT>(lines, g, st, d, step);
   }
   if constexpr (AX == AX_T) {
     if (nl == NL_BOTH) return launch_batched_rk4<N1, N2, AX, NF, NL_BOTH>(lines, g, st, d, step);

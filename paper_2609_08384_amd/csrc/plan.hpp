@@ -155,15 +155,22 @@ struct StepPasses {
   int nl[5];
 };
 StepPasses step_passes(const brahms_plan_s& p);
+// Whether steps with literal half-steps alternate their axis order (odd step
+// indices run it backwards, whatever call they belong to), so that the end of
+// one step and the beginning of the next are along one axis and run as one
+// pass: steps of two or three passes.
+bool pairing(const brahms_plan_s& p);
 // One z-step with the tables of `row`; with continued = true the step's first
-// half-step is left out (it was merged into the previous step's second one).
-brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool continued = false);
-// One step of a call with fused step pairs (tables of `row`, and of row + 1
-// unless `last`): the call's first step adds its first half-step and first
+// half-step is left out (it was merged into the previous step's second one);
+// with odd = true its axes are taken backwards.
+brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool continued, bool odd);
+// One step of a run of fused step pairs (tables of `row`, and of row + 1
+// unless `last`): the run's first step adds its first half-step and first
 // axis, every step runs its middle axis, then either its own second
-// half-step on its last axis (the call's last step) or the fused pass of its
-// last axis, the merged RK4 step and step n+1's first axis.  Steps with `odd`
-// set run the schedule's axes in reverse order.
+// half-step on its last axis (the run's last step) or the fused pass of its
+// last axis, the merged RK4 step (literal half-steps: the two half-steps) and
+// step n+1's first axis.  Steps with `odd` set run the schedule's axes in
+// reverse order.
 brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last, bool odd);
 // The axis of the k-th pass of a step (k = 0, 1, 2) under the plan's order.
 int pass_axis(const brahms_plan_s& p, int k);
@@ -171,7 +178,9 @@ int pass_axis(const brahms_plan_s& p, int k);
 brahms_status launch_linear_pass(brahms_plan_s& p, int row, int axis, float2* const* fields,
                                  bool conj);
 const float2* table_row(const brahms_plan_s& p, int row);
-// Monitor records and snapshots due once `step_done` steps are complete.
+// Whether monitor records or snapshots are due once `step_done` steps are
+// complete; and the records and snapshots themselves.
+bool step_watched(const brahms_plan_s& p, long long step_done);
 brahms_status after_step(brahms_plan_s& p, long long step_done);
 const float2* nl_coefficients(const brahms_plan_s& p, int row, int half);
 
