@@ -50,6 +50,9 @@ constexpr int NL_FUSE = 8;
 // Added to NL_AFTER | NL_FUSE (literal half-steps): the second half-step of
 // step n and the first one of step n + 1 instead of one RK4 step over both.
 constexpr int NL_LIT = 16;
+// Added to a long tau pass whose blocks each hold lines of one value of the
+// other index (a or k_b): the plane is a multiple of a block's lines.
+constexpr int NL_ONE = 32;
 
 struct PassArgs {
   float2* f[3];          // fields read (complex64, [nt][ny][nx])
@@ -578,8 +581,10 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   __shared__ float2 s_tw2[FUSE ? N : 1];
   __shared__ float2 s_prop2[FUSE ? NF * N : 1];
   // long tau axis: the nt-point twiddles (a and b passes) or the tau
-  // propagator (transform pass) of the whole axis
-  __shared__ float2 s_long[LONG ? kMaxLongT : 1];
+  // propagator (transform pass); the N entries of the block's value of the
+  // other index where it has one (ONE), else those of the whole axis
+  constexpr bool ONE = (NL & NL_ONE) != 0;
+  __shared__ float2 s_long[LONG ? (ONE ? N : kMaxLongT) : 1];
 
   const int tid = threadIdx.x;
   float2 co[NF][kNlCoef];
@@ -646,21 +651,33 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
     const int nt = args.nt;
     const float2* whole = AX == AX_TB ? args.prop + field0 * args.field_stride + args.axis_off : args.tw;
     const float2 w_tw = args.tw[min(tid, N - 1) * (nt / N)];
-    constexpr int U = 2;   // (nt is a multiple of 2 BLOCK)
-    float2 w_long[U];
-#pragma unroll
-    for (int q = 0; q < U; ++q) w_long[q] = whole[tid + q * BLOCK];
-    load_fields();
-    if (tid < N) s_tw[tid] = w_tw;
-    for (int i = tid;; i += U * BLOCK) {
-#pragma unroll
-      for (int q = 0; q < U; ++q) {
-        if (AX == AX_TB && args.conj) w_long[q].y = -w_long[q].y;
-        s_long[i + q * BLOCK] = w_long[q];
+    if constexpr (ONE) {
+      // entry k of the block: a k_b (b passes) or k_b + B k_a (a pass)
+      const unsigned k = unsigned(min(tid, N - 1));
+      float2 w = whole[AX == AX_TB ? lidx + unsigned(nt / N) * k : (lidx * k) & unsigned(nt - 1)];
+      load_fields();
+      if (AX == AX_TB && args.conj) w.y = -w.y;
+      if (tid < N) {
+        s_tw[tid] = w_tw;
+        s_long[tid] = w;
       }
-      if (i + U * BLOCK >= nt) break;
+    } else {
+      constexpr int U = 2;   // (nt is a multiple of 2 BLOCK)
+      float2 w_long[U];
 #pragma unroll
-      for (int q = 0; q < U; ++q) w_long[q] = whole[i + (U + q) * BLOCK];
+      for (int q = 0; q < U; ++q) w_long[q] = whole[tid + q * BLOCK];
+      load_fields();
+      if (tid < N) s_tw[tid] = w_tw;
+      for (int i = tid;; i += U * BLOCK) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+          if (AX == AX_TB && args.conj) w_long[q].y = -w_long[q].y;
+          s_long[i + q * BLOCK] = w_long[q];
+        }
+        if (i + U * BLOCK >= nt) break;
+#pragma unroll
+        for (int q = 0; q < U; ++q) w_long[q] = whole[i + (U + q) * BLOCK];
+      }
     }
   } else {
     StageTables<N, NF, BLOCK, FUSE> st;
@@ -692,6 +709,12 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   }
 
   if constexpr (LONG) {
+    const unsigned nb = unsigned(args.nt) / unsigned(N);
+    auto factor = [&](int k) {   // of element k of the line
+      if constexpr (ONE) return s_long[k];
+      else if constexpr (AX == AX_TB) return s_long[lidx + nb * unsigned(k)];
+      else return s_long[(lidx * unsigned(k)) & unsigned(args.nt - 1)];
+    };
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
       if constexpr (AX == AX_TAF) {
@@ -699,19 +722,18 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
         line_fft<N1, N2, false, WL>(v[j], tw, t, lbuf, K);
 #pragma unroll
         for (int e = 0; e < N1; ++e)
-          v[j][e] = cmul(v[j][e], s_long[(lidx * unsigned(t + N2 * e)) & unsigned(args.nt - 1)]);
+          v[j][e] = cmul(v[j][e], factor(t + N2 * e));
       } else if constexpr (AX == AX_TAI) {
         // conjugate twiddle, then the inverse B-point transform
 #pragma unroll
         for (int e = 0; e < N1; ++e)
-          v[j][e] = cmulc(v[j][e], s_long[(lidx * unsigned(t + N2 * e)) & unsigned(args.nt - 1)]);
+          v[j][e] = cmulc(v[j][e], factor(t + N2 * e));
         line_fft<N1, N2, true, WL>(v[j], tw, t, lbuf, K);
       } else {
         // A-point transform over a gives frequency k = k_b + B k_a in slot k_a
         line_fft<N1, N2, false, WL>(v[j], tw, t, lbuf, K);
-        const unsigned nb = unsigned(args.nt) / unsigned(N);
 #pragma unroll
-        for (int e = 0; e < N1; ++e) v[j][e] = cmul(v[j][e], s_long[lidx + nb * unsigned(t + N2 * e)]);
+        for (int e = 0; e < N1; ++e) v[j][e] = cmul(v[j][e], factor(t + N2 * e));
         line_fft<N1, N2, true, WL>(v[j], tw, t, lbuf, K);
       }
     }
@@ -936,10 +958,25 @@ __host__ __device__ constexpr bool narrow_launch(long long lines, int n2) {
   return lines * n2 < 2LL * 1024 * 64;
 }
 
+// Whether a split has passes with the fields together at all: not with 36
+// values per lane (lengths 72 and 144), where three fields take 394 registers
+// and one block fills a CU; one field per thread is as fast or faster at any
+// size (144 x 192 x 192 and three fields, x: 229 -> 114 us; 192 x 192 x 144
+// and two, tau: 109 -> 64; 72 x 256 x 256, x: 149 / 148; 256 x 256 x 72 and
+// three, tau: 137 / 142).
+template <int N1>
+constexpr bool together_split() {
+  return N1 <= 24;
+}
+
 // Threads per block of the wide linear passes (schedule field `wide`): twice
 // the lines of a kBlock block, so y and tau rows are read in segments twice
 // as long; their LDS allows two blocks per CU.
 constexpr int kWideBlock = 2 * kBlock;
+
+__host__ __device__ inline int table_row_stride(int nf, int nx, int ny, int nt) {
+  return (nf + 1) * (nx + ny + nt) + int(sizeof(DftConsts) / sizeof(float2));
+}
 
 // Blocks per CU a pass kernel of N1 values per lane and BLOCK threads is
 // compiled for (the second argument of its launch bounds).
@@ -1047,10 +1084,6 @@ __device__ inline long table_n0(const TableArgs& a) {
 
 __device__ inline long long table_merge_last(const TableArgs& a) {
   return a.n0_dev != nullptr ? a.n0_dev[1] : a.merge_last;
-}
-
-__host__ __device__ inline int table_row_stride(int nf, int nx, int ny, int nt) {
-  return (nf + 1) * (nx + ny + nt) + int(sizeof(DftConsts) / sizeof(float2));
 }
 
 // sin and cos of a phase of any size: its part of a turn, a / (2 pi) minus the

@@ -44,7 +44,8 @@ void launch_group_long(int nl, const GroupGeom& g, hipStream_t st, const PassArg
 // Blocks of an adjoint pass over `lines` lines of length n along axis.
 inline int adjoint_blocks(int axis, long lines, int n) {
   const int n2 = kBlock / lines_per_block(n);
-  const int lpb = (narrow_launch(lines, n2) ? split_threads(n2, axis) : kBlock) / n2;
+  const bool split = narrow_launch(lines, n2) || values_per_lane(n) > 24;   // (together_split)
+  const int lpb = (split ? split_threads(n2, axis) : kBlock) / n2;
   return int((lines + lpb - 1) / lpb);
 }
 

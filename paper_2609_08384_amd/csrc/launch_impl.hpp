@@ -43,31 +43,27 @@ void launch_linear(bool wide, long lines, int nf, hipStream_t st, PassArgs a) {
 // bits either way).
 template <int N1, int N2, int AX, int NF, int NL>
 void launch_rk4(long lines, hipStream_t st, const PassArgs& a) {
-  if constexpr (!long_tau_kind(AX)) {
-    if (narrow_launch(lines, N2)) {
-      constexpr int T = split_threads(N2, AX);
-      hipLaunchKernelGGL((axis_pass_split<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0, st,
-                         a);
+  if constexpr (together_split<N1>()) {
+    if (!narrow_launch(lines, N2)) {
+      hipLaunchKernelGGL((axis_pass<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, LineGeom<N1, N2>::LPB)),
+                         dim3(kBlock), 0, st, a);
       return;
     }
   }
-  hipLaunchKernelGGL((axis_pass<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, LineGeom<N1, N2>::LPB)), dim3(kBlock), 0,
-                     st, a);
+  constexpr int T = split_threads(N2, AX);
+  hipLaunchKernelGGL((axis_pass_split<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0, st, a);
 }
 
 // Half-step modes of x, y and tau passes: the transverse map runs on x and
-// tau (and the last pass of a long tau axis), fused step pairs on a short
-// axis, both half-steps in one pass only on tau (plane waves).
+// tau, both half-steps in one pass only on tau (plane waves).
 template <int N1, int N2, int AX, int NF>
 void launch_nl_nf(int nl, long lines, hipStream_t st, const PassArgs& a) {
-  if constexpr (!long_tau_kind(AX)) {
-    if (nl == (NL_AFTER | NL_FUSE)) return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE>(lines, st, a);
-    if (nl == (NL_AFTER | NL_FUSE | NL_LIT))
-      return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT>(lines, st, a);
-    if constexpr (AX != AX_Y) {
-      if (nl == (NL_AFTER | NL_FUSE | NL_LIT | NL_MAP))
-        return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT | NL_MAP>(lines, st, a);
-    }
+  if (nl == (NL_AFTER | NL_FUSE)) return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE>(lines, st, a);
+  if (nl == (NL_AFTER | NL_FUSE | NL_LIT))
+    return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT>(lines, st, a);
+  if constexpr (AX != AX_Y) {
+    if (nl == (NL_AFTER | NL_FUSE | NL_LIT | NL_MAP))
+      return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT | NL_MAP>(lines, st, a);
   }
   if constexpr (AX == AX_T) {
     if (nl == NL_BOTH) return launch_rk4<N1, N2, AX, NF, NL_BOTH>(lines, st, a);
@@ -111,22 +107,39 @@ hipError_t launch_axis(int axis, int nl, int nf, const brahms_plan_s& p, PassArg
   return hipGetLastError();
 }
 
+// The three passes of a long tau axis.  ONE: the plane is a multiple of a
+// block's lines, so that a block's lines share the other index and need only
+// N entries of the nt-point table instead of all of it (at nt = 1024, 8 KB
+// for every 16 KB of field values, and 32 KB of LDS that keep blocks off the
+// CU): 128 x 128 x 1024 and three fields, 193 / 181 / 193 -> 171 / 144 / 171
+// us; 64 x 64 x 4096, 210 / 201 / 209 -> 167 / 156 / 167 us.
+template <int N1, int N2, int AX, int NF, int NL>
+void launch_long_pass(bool one, dim3 grid, hipStream_t st, const PassArgs& a) {
+  if (one) hipLaunchKernelGGL((axis_pass<N1, N2, AX, NF, NL | NL_ONE>), grid, dim3(kBlock), 0, st, a);
+  else hipLaunchKernelGGL((axis_pass<N1, N2, AX, NF, NL>), grid, dim3(kBlock), 0, st, a);
+}
+
 template <int N1, int N2, int AX>
 hipError_t launch_long(int nl, int nf, const brahms_plan_s& p, PassArgs a) {
-  using G = LineGeom<N1, N2>;
+  constexpr int LPB = LineGeom<N1, N2>::LPB;
   a.tile_mul = 1;
   a.tiles = 1;
-  const long lines = long(p.nx) * p.ny * (p.nt / G::N);
+  const long plane = long(p.nx) * p.ny;
+  const bool one = plane % LPB == 0;
+  const unsigned blocks = blocks_of(plane * (p.nt / (N1 * N2)), LPB);
   if constexpr (AX == AX_TAI) {
-    if (nl != NL_NONE) {
-      launch_nl<N1, N2, AX_TAI>(nf, nl, lines, p.stream, a);
+    if (nl != NL_NONE) {   // the last pass of a step, with its second half-step
+      const bool map = (nl & NL_MAP) != 0;
+      if (nf == 3 && map) launch_long_pass<N1, N2, AX_TAI, 3, NL_AFTER | NL_MAP>(one, dim3(blocks), p.stream, a);
+      else if (nf == 3) launch_long_pass<N1, N2, AX_TAI, 3, NL_AFTER>(one, dim3(blocks), p.stream, a);
+      else if (map) launch_long_pass<N1, N2, AX_TAI, 2, NL_AFTER | NL_MAP>(one, dim3(blocks), p.stream, a);
+      else launch_long_pass<N1, N2, AX_TAI, 2, NL_AFTER>(one, dim3(blocks), p.stream, a);
       return hipGetLastError();
     }
   }
   // linear passes (the inverse b pass too, when fused step pairs carry the
   // RK4 step on x and y): one field per block
-  hipLaunchKernelGGL((axis_pass<N1, N2, AX, 1, NL_NONE>), dim3(blocks_of(lines, G::LPB), 1, unsigned(nf)),
-                     dim3(kBlock), 0, p.stream, a);
+  launch_long_pass<N1, N2, AX, 1, NL_NONE>(one, dim3(blocks, 1, unsigned(nf)), p.stream, a);
   return hipGetLastError();
 }
 
@@ -143,29 +156,24 @@ void launch_batched_linear(long lines, const GroupGeom& g, hipStream_t st, const
 // As launch_rk4, the lines of the whole group counted.
 template <int N1, int N2, int AX, int NF, int NL>
 void launch_batched_rk4(long lines, const GroupGeom& g, hipStream_t st, const PassArgs* d, long long step) {
-  if constexpr (!long_tau_kind(AX)) {
-    if (narrow_launch((long long)lines * g.m, N2)) {
-      constexpr int T = split_threads(N2, AX);
-      hipLaunchKernelGGL((axis_pass_split_batched<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, T / N2), g.m),
-                         dim3(NF * T), 0, st, d, step, NF);
+  if constexpr (together_split<N1>()) {
+    if (!narrow_launch((long long)lines * g.m, N2)) {
+      hipLaunchKernelGGL((axis_pass_batched<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, LineGeom<N1, N2>::LPB), g.m),
+                         dim3(kBlock), 0, st, d, step, NF);
       return;
     }
   }
-  hipLaunchKernelGGL((axis_pass_batched<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, LineGeom<N1, N2>::LPB), g.m),
-                     dim3(kBlock), 0, st, d, step, NF);
+  constexpr int T = split_threads(N2, AX);
+  hipLaunchKernelGGL((axis_pass_split_batched<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, T / N2), g.m), dim3(NF * T),
+                     0, st, d, step, NF);
 }
 
 template <int N1, int N2, int AX, int NF>
 void launch_batched_nl_nf(int nl, long lines, const GroupGeom& g, hipStream_t st, const PassArgs* d, long long step) {
-  if constexpr (!long_tau_kind(AX)) {
-    if (nl == (NL_AFTER | NL_FUSE))
-      return launch_batched_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE>(lines, g, st, d, step);
-    if (nl == (NL_AFTER | NL_FUSE | NL_LIT))
-      return launch_batched_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT>(lines, g, st, d, step);
-  }
-  if constexpr (AX == AX_T) {
-    if (nl == NL_BOTH) return launch_batched_rk4<N1, N2, AX, NF, NL_BOTH>(lines, g, st, d, step);
-  }
+  if (nl == (NL_AFTER | NL_FUSE))
+    return launch_batched_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE>(lines, g, st, d, step);
+  if (nl == (NL_AFTER | NL_FUSE | NL_LIT))
+    return launch_batched_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT>(lines, g, st, d, step);
   if (nl == NL_BEFORE) launch_batched_rk4<N1, N2, AX, NF, NL_BEFORE>(lines, g, st, d, step);
   else launch_batched_rk4<N1, N2, AX, NF, NL_AFTER>(lines, g, st, d, step);
 }
@@ -201,11 +209,27 @@ void launch_group_pass(int axis, int nl, const GroupGeom& g, hipStream_t st, con
   else launch_group_axis<N1, N2, AX_T>(nl, long(g.nx) * g.ny, g, st, d, step);
 }
 
+template <int N1, int N2, int AX, int NF, int NL>
+void launch_group_long_pass(bool one, dim3 grid, const GroupGeom& g, hipStream_t st, const PassArgs* d,
+                            long long step) {
+  if (one)
+    hipLaunchKernelGGL((axis_pass_batched<N1, N2, AX, NF, NL | NL_ONE>), grid, dim3(kBlock), 0, st, d, step, g.nf);
+  else
+    hipLaunchKernelGGL((axis_pass_batched<N1, N2, AX, NF, NL>), grid, dim3(kBlock), 0, st, d, step, g.nf);
+}
+
 template <int N1, int N2, int AX>
 void launch_group_long(int nl, const GroupGeom& g, hipStream_t st, const PassArgs* d, long long step) {
-  const long lines = long(g.nx) * g.ny * (g.nt / (N1 * N2));
-  if constexpr (AX == AX_TAI) launch_batched_nl<N1, N2, AX_TAI>(nl, lines, g, st, d, step);
-  else launch_batched_linear<N1, N2, AX>(lines, g, st, d, step);
+  constexpr int LPB = LineGeom<N1, N2>::LPB;
+  const long plane = long(g.nx) * g.ny;
+  const bool one = plane % LPB == 0;
+  const unsigned blocks = blocks_of(plane * (g.nt / (N1 * N2)), LPB);
+  if constexpr (AX == AX_TAI) {   // (groups of long tau problems keep their five passes)
+    if (g.nf == 3) launch_group_long_pass<N1, N2, AX_TAI, 3, NL_AFTER>(one, dim3(blocks, g.m), g, st, d, step);
+    else launch_group_long_pass<N1, N2, AX_TAI, 2, NL_AFTER>(one, dim3(blocks, g.m), g, st, d, step);
+  } else {
+    launch_group_long_pass<N1, N2, AX, 1, NL_NONE>(one, dim3(blocks, 1, unsigned(g.nf) * g.m), g, st, d, step);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -215,16 +239,18 @@ template <int N1, int N2, int AX, int NF, int AT>
 void launch_adj(const brahms_plan_s& p, const AdjArgs& a) {
   const long lines = AX == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
   // (the block counts are adjoint_blocks' in launch.hpp)
-  if (narrow_launch(lines, N2)) {
-    constexpr int T = split_threads(N2, AX);
-    hipLaunchKernelGGL((adjoint_pass_split<N1, N2, AX, NF, AT>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0,
-                       p.stream, a);
-    return;
+  if constexpr (together_split<N1>()) {
+    if (!narrow_launch(lines, N2)) {
+      const dim3 grid(blocks_of(lines, LineGeom<N1, N2>::LPB));
+      AdjArgs b = a;
+      b.tile_mul = AX == AX_T ? tile_multiplier(grid.x) : 1u;
+      hipLaunchKernelGGL((adjoint_pass<N1, N2, AX, NF, AT>), grid, dim3(kBlock), 0, p.stream, b);
+      return;
+    }
   }
-  const dim3 grid(blocks_of(lines, LineGeom<N1, N2>::LPB));
-  AdjArgs b = a;
-  b.tile_mul = AX == AX_T ? tile_multiplier(grid.x) : 1u;
-  hipLaunchKernelGGL((adjoint_pass<N1, N2, AX, NF, AT>), grid, dim3(kBlock), 0, p.stream, b);
+  constexpr int T = split_threads(N2, AX);
+  hipLaunchKernelGGL((adjoint_pass_split<N1, N2, AX, NF, AT>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0,
+                     p.stream, a);
 }
 
 template <int N1, int N2>
