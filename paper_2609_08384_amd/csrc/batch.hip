@@ -283,6 +283,27 @@ void dispatch_group_pass(int len, int axis, int nl, const brahms_batch_s::Group&
   }
 }
 
+void dispatch_group_line(const brahms_batch_s::Group& g, unsigned m, hipStream_t st, const PassArgs* d,
+                         long long step, int count, bool merged) {
+  const int n = g.axis_len[2];
+  if (((g.split >> AX_T) & 1) && has_alt_split(n)) {
+    switch (n) {
+#define BRAHMS_CASE_(N, N1, N2) \
+  case N: brahms::detail::launch_group_line_steps<N1, N2>(g.nf, m, st, d, step, count, merged); return;
+      BRAHMS_ALT_LENGTHS(BRAHMS_CASE_)
+#undef BRAHMS_CASE_
+      default: break;
+    }
+  }
+  switch (n) {
+#define BRAHMS_CASE_(N, N1, N2) \
+  case N: brahms::detail::launch_group_line_steps<N1, N2>(g.nf, m, st, d, step, count, merged); break;
+    BRAHMS_LENGTHS(BRAHMS_CASE_)
+#undef BRAHMS_CASE_
+    default: break;
+  }
+}
+
 // Host images of the descriptors (pass arguments per slot and table
 // arguments per chunk) of every group, uploaded once at bind.
 brahms_status upload_descriptors(brahms_batch_s& b) {
@@ -390,6 +411,12 @@ brahms_status enqueue_group(brahms_batch_s& b, const brahms_batch_s::Group& g, h
       const int cnt = std::min(kChunk, g.max_steps - c * kChunk);
       const brahms::detail::StepPasses sp = brahms::detail::step_passes(p0);
       const int end = sp.n - 1;
+      if (sp.n == 1) {   // plane waves: the chunk's steps in one launch
+        const PassArgs* d = reinterpret_cast<const PassArgs*>(b.ws + b.off_desc + g.desc_off);
+        dispatch_group_line(g, m, st, d, (long long)c * kChunk, cnt, b.merge);
+        HIP_TRY(hipGetLastError());
+        continue;
+      }
       for (int s = 0; s < cnt; ++s) {
         const long long step = (long long)c * kChunk + s;
         for (int pass = 0; pass < sp.n; ++pass) {

@@ -440,6 +440,41 @@ brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last
   return timed_dispatch(p, tail, NL_AFTER | NL_FUSE | (literal ? NL_LIT | map_mode : 0), a);
 }
 
+brahms_status launch_line(brahms_plan_s& p, int row, int count, bool continued) {
+  PassArgs a = pass_args(p, row, AX_T);
+  for (int j = 0; j < 3; ++j) {
+    a.f[j] = p.fields[j];
+    a.fo[j] = p.fields[j];
+  }
+  a.nl = nl_coefficients(p, row, 0);
+  a.nl2 = nl_coefficients(p, row, 1);
+  const bool alt = ((p.split >> AX_T) & 1) != 0, merged = merging(p);
+  const bool timed = p.timing && p.timed.size() < kMaxTimed;
+  if (brahms_status st = timing_start(p, AX_T)) return st;
+  hipError_t e = hipErrorInvalidValue;
+  if (alt && has_alt_split(p.nt)) {
+    switch (p.nt) {
+#define BRAHMS_CASE_(N, N1, N2) \
+  case N: e = launch_line_steps<N1, N2>(p, a, count, merged, !continued); break;
+      BRAHMS_ALT_LENGTHS(BRAHMS_CASE_)
+#undef BRAHMS_CASE_
+      default: break;
+    }
+  } else {
+    switch (p.nt) {
+#define BRAHMS_CASE_(N, N1, N2) \
+  case N: e = launch_line_steps<N1, N2>(p, a, count, merged, !continued); break;
+      BRAHMS_LENGTHS(BRAHMS_CASE_)
+#undef BRAHMS_CASE_
+      default: break;
+    }
+  }
+  HIP_TRY(e);
+  if (timed)
+    if (brahms_status st = timing_stop(p)) return st;
+  return BRAHMS_OK;
+}
+
 brahms_status launch_linear_pass(brahms_plan_s& p, int row, int axis, float2* const* fields,
                                  bool conj) {
   if (axis != AX_Y) return fail(BRAHMS_E_INVALID_ARG, "linear-only passes run along y");
@@ -504,8 +539,10 @@ brahms_status build_chunk_graph(brahms_plan_s& p) {
         st = detail::launch_fused_step(p, s, false, false, (s & 1) != 0);
     } else {
       const bool continued = detail::merging(p), pairs = detail::pairing(p);
+      const bool line = !detail::long_tau(p) && detail::step_passes(p).n == 1;
       st = detail::refresh_tables(p, 0, kChunk);
-      for (int s = 0; s < kChunk && st == BRAHMS_OK; ++s)
+      if (line && st == BRAHMS_OK) st = detail::launch_line(p, 0, kChunk, continued);
+      for (int s = 0; s < kChunk && st == BRAHMS_OK && !line; ++s)
         st = pairs ? detail::launch_fused_step(p, s, s == 0, s == kChunk - 1, (s & 1) != 0)   // (from an even step)
                    : detail::launch_step(p, s, io, continued, false);
     }
@@ -583,6 +620,7 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
   // snapshot looks at (the same bits wherever a run ends)
   const bool pairs = detail::pairing(p);
   const bool row_maps = p.dk_map.empty() || p.map_rows == kChunk;
+  const bool line = !detail::long_tau(p) && detail::step_passes(p).n == 1;
   const long long merge_last = merge ? p.step + nsteps - 1 : -1;
   int done = 0;
   while (done < nsteps) {
@@ -606,7 +644,18 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
     if (brahms_status st = detail::refresh_tables(p, p.step, count, 0, merge_last)) return st;
     const bool watch = p.mon_every > 0 || !p.snap_steps.empty();
     bool open = false;   // the previous step's last pass began this step
-    for (int s = 0; s < count; ++s) {
+    if (line) {
+      // a plane wave: all steps up to one that is looked at in one launch
+      for (int s = 0; s < count;) {
+        int e = s + 1;
+        while (e < count && !(watch && detail::step_watched(p, p.step + e))) ++e;
+        if (brahms_status st = detail::launch_line(p, s, e - s, merge && (done > 0 || s > 0))) return st;
+        if (watch)
+          if (brahms_status st = detail::after_step(p, p.step + e)) return st;
+        s = e;
+      }
+    }
+    for (int s = 0; s < count && !line; ++s) {
       const long long n = p.step + s;
       if (pairs) {
         const bool last = s == count - 1 || !row_maps || (watch && detail::step_watched(p, n + 1));

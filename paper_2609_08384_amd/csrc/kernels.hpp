@@ -1036,6 +1036,101 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void axis_pass_split_
 }
 
 // ---------------------------------------------------------------------------
+// Plane waves (nx = ny = 1): the field is one tau line, nothing else depends
+// on it, and a block keeps it in registers over `count` steps: half-step, FFT
+// . P . IFFT, half-step, with the tables of consecutive rows (args: the first
+// one's).  merged: a step's first half-step is part of the previous one's
+// second; `first` says whether the first step here has its own.  One wave per
+// field transforms (its lanes past the line repeat it), and the RK4 points
+// are spread over all the block's threads; a step's time is this serial chain
+// (no memory traffic to speak of), with the next step's tables loaded beside
+// it.  nt = 256, two fields, literal half-steps: 19.5 us a step as a launch
+// per step of one wave of 32 values a lane, 10.5 us with one field per wave.
+// ---------------------------------------------------------------------------
+template <int N1, int N2, int NF>
+__device__ __forceinline__ void line_steps_body(const PassArgs& args, int count, bool merged, bool first) {
+  constexpr int T = 64, BLOCK = NF * T;
+  using G = LineGeom<N1, N2, T>;
+  constexpr int N = G::N;
+  static_assert(N2 <= T, "a line within one wave");
+  __shared__ float2 lds[NF * (N2 > 1 ? G::LDS_ELEMS : 1)];
+  __shared__ float2 s_val[NF][N];
+  __shared__ float2 s_tw[N], s_prop[NF * N];
+  const int tid = threadIdx.x;
+  const int f = __builtin_amdgcn_readfirstlane(tid / T);
+  const int t = tid % N2, li = tid % T / N2;
+  const int row = table_row_stride(NF, 1, 1, N);
+  float2* lbuf = (N2 > 1) ? lds + f * G::LDS_ELEMS + li * G::LSTRIDE : lds;
+  const __amdgpu_buffer_rsrc_t r = field_rsrc(args.f[f], unsigned(N) * 8u);
+  const unsigned lane_bytes = unsigned(t) * 8u;
+  PassArgs a = args;   // (advanced row by row)
+  StageTables<N, NF, BLOCK, false> st;
+  st.begin(a, 0, tid);
+  float2 v[1][N1];
+#pragma unroll
+  for (int e = 0; e < N1; ++e) v[0][e] = load_slot<false>(r, lane_bytes, unsigned(N2 * e) * 8u);
+  LaneTwiddles<N1, N2, true> tw;
+
+  auto rk4 = [&](const float2* nl) {
+    float2 co[NF][kNlCoef];
+    load_coefficients<NF>(nl, co);
+    if (li == 0) {
+#pragma unroll
+      for (int e = 0; e < N1; ++e) s_val[f][t + N2 * e] = v[0][e];
+    }
+    __syncthreads();
+    for (int q = tid; q < N; q += BLOCK) {
+      float2 y[NF];
+#pragma unroll
+      for (int j = 0; j < NF; ++j) y[j] = s_val[j][q];
+      rk4_point<NF>(y, co);
+#pragma unroll
+      for (int j = 0; j < NF; ++j) s_val[j][q] = y[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < N1; ++e) v[0][e] = s_val[f][t + N2 * e];
+  };
+  for (int s = 0; s < count; ++s) {
+    __syncthreads();   // the previous step's tables and values are read
+    st.end(false, tid, s_tw, s_prop, s_tw, s_prop);
+    const DftConsts K = *a.consts;
+    const float2 *nl = a.nl, *nl2 = a.nl2;
+    a.tw += row;
+    a.prop += row;
+    a.consts = reinterpret_cast<const DftConsts*>(reinterpret_cast<const float2*>(a.consts) + row);
+    a.nl += 2 * NF * kNlCoef;
+    a.nl2 += 2 * NF * kNlCoef;
+    if (s + 1 < count) st.begin(a, 0, tid);
+    if (!merged || (s == 0 && first)) rk4(nl);   // (its barriers stand behind the tables')
+    else __syncthreads();
+    tw.init(s_tw, t);
+    line_trip<N1, N2, 1, true, false>(v, tw, t, lbuf, s_prop + f * N, K);
+    rk4(nl2);
+  }
+  if (li == 0) {
+    const __amdgpu_buffer_rsrc_t ro = field_rsrc(args.fo[f], unsigned(N) * 8u);
+#pragma unroll
+    for (int e = 0; e < N1; ++e) store_slot<false>(ro, lane_bytes, unsigned(N2 * e) * 8u, v[0][e]);
+  }
+}
+
+template <int N1, int N2, int NF>
+__global__ __launch_bounds__(NF * 64) void line_steps(PassArgs args, int count, int merged, int first) {
+  line_steps_body<N1, N2, NF>(args, count, merged != 0, first != 0);
+}
+
+// Steps step .. step + count - 1 of a group (descs: of the first step).
+template <int N1, int N2, int NF>
+__global__ __launch_bounds__(NF * 64) void line_steps_batched(const PassArgs* descs, long long step, int count,
+                                                              int merged) {
+  const PassArgs& a = descs[blockIdx.x];
+  const long long left = a.nz - step;
+  if (left <= 0) return;
+  line_steps_body<N1, N2, NF>(a, int(min((long long)count, left)), merged != 0, step == 0);
+}
+
+// ---------------------------------------------------------------------------
 // Per-step tables, formed in double precision.
 //
 // Propagator of field j along one axis for step n (z_n = n dz):

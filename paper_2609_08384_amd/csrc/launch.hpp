@@ -19,6 +19,14 @@ namespace detail {
 template <int N1, int N2>
 hipError_t launch_axis(int axis, int nl, int nf, const brahms_plan_s& p, PassArgs a);
 
+// `count` steps of a plane wave (nt = N1 N2) from the row of a, and of a
+// group of them from descriptors d.
+template <int N1, int N2>
+hipError_t launch_line_steps(const brahms_plan_s& p, const PassArgs& a, int count, bool merged, bool first);
+template <int N1, int N2>
+void launch_group_line_steps(int nf, unsigned m, hipStream_t st, const PassArgs* d, long long step, int count,
+                             bool merged);
+
 // One of the three passes of a long tau axis (sub-transforms N1 N2).
 template <int N1, int N2, int AX>
 hipError_t launch_long(int nl, int nf, const brahms_plan_s& p, PassArgs a);

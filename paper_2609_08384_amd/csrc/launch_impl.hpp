@@ -107,6 +107,24 @@ hipError_t launch_axis(int axis, int nl, int nf, const brahms_plan_s& p, PassArg
   return hipGetLastError();
 }
 
+template <int N1, int N2>
+hipError_t launch_line_steps(const brahms_plan_s& p, const PassArgs& a, int count, bool merged, bool first) {
+  if (p.nf == 3)
+    hipLaunchKernelGGL((line_steps<N1, N2, 3>), dim3(1), dim3(192), 0, p.stream, a, count, int(merged), int(first));
+  else
+    hipLaunchKernelGGL((line_steps<N1, N2, 2>), dim3(1), dim3(128), 0, p.stream, a, count, int(merged), int(first));
+  return hipGetLastError();
+}
+
+template <int N1, int N2>
+void launch_group_line_steps(int nf, unsigned m, hipStream_t st, const PassArgs* d, long long step, int count,
+                             bool merged) {
+  if (nf == 3)
+    hipLaunchKernelGGL((line_steps_batched<N1, N2, 3>), dim3(m), dim3(192), 0, st, d, step, count, int(merged));
+  else
+    hipLaunchKernelGGL((line_steps_batched<N1, N2, 2>), dim3(m), dim3(128), 0, st, d, step, count, int(merged));
+}
+
 // The three passes of a long tau axis.  ONE: the plane is a multiple of a
 // block's lines, so that a block's lines share the other index and need only
 // N entries of the nt-point table instead of all of it (at nt = 1024, 8 KB
@@ -284,6 +302,12 @@ void launch_adj_axis(int axis, int at, const brahms_plan_s& p, const AdjArgs& a)
   template void brahms::detail::launch_group_pass<N1, N2>(int, int, const brahms::detail::GroupGeom&, \
                                                           hipStream_t, const brahms::PassArgs*,        \
                                                           long long);                                  \
+  template hipError_t brahms::detail::launch_line_steps<N1, N2>(const brahms_plan_s&,                 \
+                                                                const brahms::PassArgs&, int, bool,   \
+                                                                bool);                                \
+  template void brahms::detail::launch_group_line_steps<N1, N2>(int, unsigned, hipStream_t,           \
+                                                                const brahms::PassArgs*, long long,   \
+                                                                int, bool);                           \
   template void brahms::detail::launch_adj_axis<N1, N2>(int, int, const brahms_plan_s&,               \
                                                         const brahms::AdjArgs&);
 

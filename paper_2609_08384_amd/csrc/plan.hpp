@@ -172,6 +172,10 @@ brahms_status launch_step(brahms_plan_s& p, int row, const StepIO& io, bool cont
 // step n+1's first axis.  Steps with `odd` set run the schedule's axes in
 // reverse order.
 brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last, bool odd);
+// `count` steps of a plane wave (steps of one pass) with the tables of rows
+// row .. row + count - 1; with continued = true the first step's first
+// half-step is left out.
+brahms_status launch_line(brahms_plan_s& p, int row, int count, bool continued);
 // The axis of the k-th pass of a step (k = 0, 1, 2) under the plan's order.
 int pass_axis(const brahms_plan_s& p, int k);
 // A linear-only pass (FFT . P . IFFT, or with conj(P)) along `axis`, in place.
