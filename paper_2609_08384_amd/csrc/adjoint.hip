@@ -8,8 +8,10 @@
 // into a second set of buffers, while the previous segment is swept back);
 // then for each step in reverse apply
 // the adjoint passes (reverse second half-step + conj-propagator transforms
-// along the last axis, conj-propagator transforms along y, conj-propagator
-// transforms along the first axis + reverse first half-step).  dJ/dPhi at the
+// along one axis, conj-propagator transforms along y, conj-propagator
+// transforms along the other axis + reverse first half-step); the axes
+// alternate, so that the end of one step and the beginning of the next are
+// one pass.  dJ/dPhi at the
 // six stage positions of every step is reduced on the device in a fixed
 // order and turned into dJ/ddk_n on the host: with Phi(z) = Phi_n +
 // dk_n (z - z_n) and Phi_n = dz sum_{m<n} dk_m,
@@ -106,35 +108,46 @@ brahms_status copy_state(const brahms_plan_s& p, float2* const* dst, float2* con
   return BRAHMS_OK;
 }
 
-// One adjoint pass with an RK4 reverse sweep; its per-block phase
-// derivatives go to slot (row, k == 0 ? 0 : 1) of the segment's partials.
-brahms_status adj_pass(brahms_plan_s& p, const AdjLayout& L, int set, int row, int k,
-                       float2* const* g, float2* const* y) {
-  const int ax = brahms::detail::pass_axis(p, k);
+// One adjoint pass along ax with the reverse RK4 of step `row`'s second
+// half-step (at = VJP_FIRST), of its first one (VJP_LAST), or of its first one
+// and step row - 1's second one (VJP_PAIR).  Their inputs are the segment's
+// saved ones; their per-block phase derivatives go to slots (row, 1), (row, 0)
+// and (row - 1, 1) of its partials.
+brahms_status adj_pass(brahms_plan_s& p, const AdjLayout& L, int set, int row, int ax, int at,
+                       float2* const* g) {
   const int per_field = p.nx + p.ny + p.nt;
-  const int trow = set * kSetRows + row;
-  const float2* r = brahms::detail::table_row(p, trow);
+  const int trow = set * kSetRows + row, half = at == VJP_FIRST ? 1 : 0;
+  double* parts = reinterpret_cast<double*>(p.adj_ws + L.parts[set]);
+  auto slot = [&](int r, int h) { return parts + (size_t(r) * 2 + h) * size_t(L.max_blocks) * 3; };
   AdjArgs a{};
-  for (int j = 0; j < 3; ++j) {
-    a.g[j] = j < p.nf ? g[j] : nullptr;
-    a.y[j] = j < p.nf ? y[j] : nullptr;
+  for (int j = 0; j < p.nf; ++j) {
+    a.g[j] = g[j];
+    a.y[j] = state_field(p.adj_ws + (half ? L.pre[set] : L.seg[set]), L, p, row, j);
   }
   a.axis_off = ax == AX_X ? 0 : p.nx + p.ny;
-  a.tw = r + p.nf * per_field + a.axis_off;
-  a.consts = reinterpret_cast<const DftConsts*>(r + (p.nf + 1) * per_field);
-  a.prop = r;
+  auto tables = [&](int tr, const float2*& tw, const float2*& prop, const DftConsts*& consts) {
+    prop = brahms::detail::table_row(p, tr);
+    tw = prop + p.nf * per_field + a.axis_off;
+    consts = reinterpret_cast<const DftConsts*>(prop + (p.nf + 1) * per_field);
+  };
+  tables(trow, a.tw, a.prop, a.consts);
+  a.nl = brahms::detail::nl_coefficients(p, trow, half);
+  a.dphi_out = slot(row, half);
+  if (at == VJP_PAIR) {
+    for (int j = 0; j < p.nf; ++j) a.y2[j] = state_field(p.adj_ws + L.pre[set], L, p, row - 1, j);
+    tables(trow - 1, a.tw2, a.prop2, a.consts2);
+    a.nl2 = brahms::detail::nl_coefficients(p, trow - 1, 1);
+    a.dphi_out2 = slot(row - 1, 1);
+  }
   a.field_stride = per_field;
-  a.nl = brahms::detail::nl_coefficients(p, trow, k == 0 ? 0 : 1);
   a.nx = p.nx; a.ny = p.ny; a.nt = p.nt;
-  double* parts = reinterpret_cast<double*>(p.adj_ws + L.parts[set]);
-  a.dphi_out = parts + (size_t(row) * 2 + (k == 0 ? 0 : 1)) * size_t(L.max_blocks) * 3;
   // exp(-i Phi) on the sum-frequency field, exp(+i Phi) on the others
   if (p.nf == 3) {
     a.sigma[0] = -1.f; a.sigma[1] = 1.f; a.sigma[2] = 1.f;
   } else {
     a.sigma[0] = 1.f; a.sigma[1] = -1.f; a.sigma[2] = 0.f;
   }
-  HIP_TRY(dispatch_adj(ax, k == 0 ? VJP_LAST : VJP_FIRST, p, a));
+  HIP_TRY(dispatch_adj(ax, at, p, a));
   return BRAHMS_OK;
 }
 
@@ -178,21 +191,19 @@ brahms_status reverse_segment(brahms_plan_s& p, const AdjLayout& L, int c, int s
                               double* dphi) {
   const long long s0 = p.adj_n0 + (long long)c * p.adj_every;
   const int cnt = int(std::min<long long>(p.adj_every, p.adj_n0 + p.adj_nsteps - s0));
+  // The sweep takes the axes of every other step the other way round (they
+  // commute), so that the last axis of one step is the first of the next one
+  // it comes to, and one pass does both.
+  const int ends[2] = {brahms::detail::pass_axis(p, 2), brahms::detail::pass_axis(p, 0)};
+  if (brahms_status st = adj_pass(p, L, set, cnt - 1, ends[0], VJP_FIRST, g)) return st;
   for (int i = cnt - 1; i >= 0; --i) {
-    float2* y2[3] = {nullptr, nullptr, nullptr};
-    float2* y0[3] = {nullptr, nullptr, nullptr};
-    for (int j = 0; j < p.nf; ++j) {
-      y2[j] = state_field(p.adj_ws + L.pre[set], L, p, i, j);
-      y0[j] = state_field(p.adj_ws + L.seg[set], L, p, i, j);
-    }
-    if (brahms_status st = adj_pass(p, L, set, i, 2, g, y2)) return st;
     if (brahms_status st = brahms::detail::launch_linear_pass(p, set * kSetRows + i, AX_Y, g, true))
       return st;
-    if (brahms_status st = adj_pass(p, L, set, i, 0, g, y0)) return st;
+    const int ax = ends[(cnt - i) & 1];
+    if (brahms_status st = adj_pass(p, L, set, i, ax, i > 0 ? VJP_PAIR : VJP_LAST, g)) return st;
   }
   // dJ/dPhi of the segment's steps, in a fixed order
-  const int nb_first = pass_blocks(brahms::detail::pass_axis(p, 0), p);
-  const int nb_last = pass_blocks(brahms::detail::pass_axis(p, 2), p);
+  const int nb_first = pass_blocks(ends[1], p), nb_last = pass_blocks(ends[0], p);
   hipLaunchKernelGGL(reduce_dphi_segment, dim3(unsigned(cnt), 2), dim3(256), 0, p.stream,
                      reinterpret_cast<const double*>(p.adj_ws + L.parts[set]), nb_first, nb_last,
                      L.max_blocks, dphi + 6 * (s0 - p.adj_n0));

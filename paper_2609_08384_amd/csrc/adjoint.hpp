@@ -116,11 +116,14 @@ __device__ inline void rk4_vjp_point(const float2* y, float2* g, const float2 (*
 //              half-step came after its transforms): reverse RK4 with the
 //              saved half-step input, then FFT . conj(P) . IFFT;
 //   VJP_LAST:  the pass undoes the first pass of a forward step: FFT .
-//              conj(P) . IFFT, then reverse RK4 with the step's input.
-// g is updated in place; the block's three dJ/dPhi partial sums (fixed-order
-// reduction in double) go to dphi_out[block].
+//              conj(P) . IFFT, then reverse RK4 with the step's input;
+//   VJP_PAIR:  VJP_LAST of step n, then VJP_FIRST of step n - 1, along the
+//              same axis (the axes of a step's linear part commute, so the
+//              reverse sweep takes them in an order of its own).
+// g is updated in place; the block's dJ/dPhi partial sums (fixed-order
+// reduction in double) go to dphi_out[block], three for each reverse RK4.
 // ---------------------------------------------------------------------------
-enum VjpWhere { VJP_FIRST = 1, VJP_LAST = 2 };
+enum VjpWhere { VJP_FIRST = 1, VJP_LAST = 2, VJP_PAIR = 3 };
 
 struct AdjArgs {
   float2* g[3];             // cotangent fields, in place
@@ -130,9 +133,14 @@ struct AdjArgs {
   const float2* nl;
   const DftConsts* consts;
   double* dphi_out;         // [gridDim.x][3]
+  const float2* y2[3];      // VJP_PAIR: those of step n - 1's second half-step
+  const float2* tw2;
+  const float2* prop2;
+  const float2* nl2;
+  const DftConsts* consts2;
+  double* dphi_out2;
   int nx, ny, nt;
   int axis_off, field_stride;
-  unsigned tile_mul;
   float sigma[3];
 };
 
@@ -158,109 +166,28 @@ __device__ __forceinline__ void reduce_dphi(const double* dphi, double (*s_red)[
   }
 }
 
+// One field per thread at every size (see axis_pass_split_body), the saved
+// half-step inputs of a thread's points loaded with its cotangents; the
+// reverse RK4 goes point by point (the asm ties: all points at once take 256
+// registers and leave one wave per SIMD).  A fields-together pass holds four
+// values per point of both fields and more; with the saved states in memory
+// (not in a cache) 128 x 128 x 64 and two fields: x last 26.4 against 18.4
+// us, x first 23.5 / 18.5, tau first 18.3 / 17.8; 128^3, x first 33.1 / 33.0,
+// tau first 33.6 / 32.2 (three fields, tau first 46.9 / 66.3, the one form
+// that lost, but x last 65.7 / 44.6).  What bounds it: six field transfers,
+// 50 MB at 128 x 128 x 64, 10 us; the rest is the chain of two waves a SIMD.
+// A pair moves eight where two passes move twelve.
 template <int N1, int N2, int AX, int NF, int AT>
-__global__ __launch_bounds__(kBlock) void adjoint_pass(AdjArgs args) {
-  using G = LineGeom<N1, N2>;
-  constexpr int N = G::N;
-  constexpr bool REG = twiddle_registers<N1, NF, kBlock>();
-  static_assert(AX == AX_X || AX == AX_T, "RK4 reverse sweeps live in the x or tau pass");
-  __shared__ float2 lds[G::LDS_ELEMS];
-  __shared__ float2 s_tw[N];
-  __shared__ float2 s_prop[NF * N];
-  __shared__ double s_red[3][kBlock];
-
-  const int tid = threadIdx.x;
-  const int t = AX == AX_X ? tid % N2 : tid / G::LPB;
-  const int li = AX == AX_X ? tid / N2 : tid % G::LPB;
-  unsigned bx = blockIdx.x;
-  if constexpr (AX == AX_T) bx = unsigned((unsigned long long)bx * args.tile_mul % gridDim.x);
-  const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
-  const unsigned idx0 = la.base + unsigned(t) * la.estride;
-  const unsigned estep = unsigned(N2) * la.estride;
-  // x lines: a line's N2 lanes are consecutive threads, within one wavefront
-  constexpr bool WL = AX == AX_X && N2 <= 64 && 64 % N2 == 0;
-  // a line's LDS row (lines of one lane exchange nothing: no row)
-  float2* lbuf = (N2 > 1) ? lds + li * G::LSTRIDE : lds;
-  const DftConsts K = *args.consts;
-  // fields through buffer resources, as in the forward passes
-  const unsigned field_bytes = unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) * 8u;
-  const unsigned lane_bytes = idx0 * 8u;
-  const unsigned slot_bytes = estep * 8u;
-  __amdgpu_buffer_rsrc_t rg[NF], ry[NF];
-#pragma unroll
-  for (int j = 0; j < NF; ++j) {
-    rg[j] = field_rsrc(args.g[j], field_bytes);
-    ry[j] = field_rsrc(args.y[j], field_bytes);
-  }
-  // RK4 coefficients: the same for every thread, in scalar registers
-  float2 co[NF][kNlCoef];
-  load_coefficients<NF>(args.nl, co);
-  float sigma[NF];
-#pragma unroll
-  for (int j = 0; j < NF; ++j) sigma[j] = args.sigma[j];
-  double dphi[3] = {0.0, 0.0, 0.0};
-
-  StageTables<N, NF, kBlock, false> st;
-  st.begin(args, 0, tid);
-  float2 v[NF][N1];
-#pragma unroll
-  for (int j = 0; j < NF; ++j)
-#pragma unroll
-    for (int e = 0; e < N1; ++e) v[j][e] = load_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes);
-  st.end(false, tid, s_tw, s_prop, s_tw, s_prop);
-  __syncthreads();  // s_tw, s_prop staged
-  LaneTwiddles<N1, N2, REG> tw;
-  tw.init(s_tw, t);
-
-  auto reverse_rk4 = [&]() {
-#pragma unroll
-    for (int e = 0; e < N1; ++e) {
-      float2 yy[NF], gg[NF];
-#pragma unroll
-      for (int j = 0; j < NF; ++j) {
-        yy[j] = load_slot<false>(ry[j], lane_bytes, unsigned(e) * slot_bytes);
-        gg[j] = v[j][e];
-      }
-      // One point at a time: tie this point's inputs to the phase sums of the
-      // previous points (an empty asm, no instructions), so the compiler
-      // cannot interleave all points and run out of registers.
-#pragma unroll
-      for (int j = 0; j < NF; ++j)
-        asm volatile("" : "+v"(yy[j].x), "+v"(yy[j].y), "+v"(gg[j].x), "+v"(gg[j].y), "+v"(dphi[0]),
-                          "+v"(dphi[1]), "+v"(dphi[2]));
-      rk4_vjp_point<NF>(yy, gg, co, sigma, dphi);
-#pragma unroll
-      for (int j = 0; j < NF; ++j) v[j][e] = gg[j];
-    }
-  };
-
-  if constexpr (AT == VJP_FIRST) reverse_rk4();
-  line_trip<N1, N2, NF, WL, true>(v, tw, t, lbuf, s_prop, K);
-  if constexpr (AT == VJP_LAST) reverse_rk4();
-  if (la.valid) {
-#pragma unroll
-    for (int j = 0; j < NF; ++j)
-#pragma unroll
-      for (int e = 0; e < N1; ++e) store_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
-  } else {
-    dphi[0] = dphi[1] = dphi[2] = 0.0;   // a line past the last one counts for nothing
-  }
-  reduce_dphi<kBlock, kBlock>(dphi, s_red, args.dphi_out);
-}
-
-// The adjoint pass with one field per thread (see axis_pass_split_body): the
-// saved half-step inputs of a thread's points are loaded at the start, with
-// its cotangents.  128 x 128 x 64 and two fields: see narrow_launch.
-template <int N1, int N2, int AX, int NF, int AT>
-__global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass_split(AdjArgs args) {
+__global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(AdjArgs args) {
   constexpr int T = split_threads(N2, AX), BLOCK = NF * T;
   using G = LineGeom<N1, N2, T>;
   constexpr int N = G::N;
   constexpr bool WL = AX == AX_X && T == 64 && N2 <= 64 && 64 % N2 == 0;
+  constexpr bool PAIR = AT == VJP_PAIR;
   static_assert(AX == AX_X || AX == AX_T, "RK4 reverse sweeps live in the x or tau pass");
   constexpr int XS = N2 > 1 ? G::LDS_ELEMS : N1 * T;
   __shared__ float2 lds[NF * XS];
-  __shared__ float2 s_tw[N], s_prop[NF * N];
+  __shared__ float2 s_tw[N], s_prop[NF * N], s_tw2[PAIR ? N : 1], s_prop2[PAIR ? NF * N : 1];
   __shared__ double s_red[3][BLOCK];
 
   const int tid = threadIdx.x;
@@ -280,43 +207,72 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass_spl
   float sigma[NF];
 #pragma unroll
   for (int j = 0; j < NF; ++j) sigma[j] = args.sigma[j];
-  double dphi[3] = {0.0, 0.0, 0.0};
 
   constexpr int P = (N1 + NF - 1) / NF;
-  StageTables<N, NF, BLOCK, false> st;
+  auto load_points = [&](const float2* const* from, float2 (&y)[P][NF]) {
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+      const __amdgpu_buffer_rsrc_t ry = field_rsrc(from[j], field_bytes);
+#pragma unroll
+      for (int k = 0; k < P; ++k)
+        y[k][j] = load_slot<false>(ry, lane_bytes, unsigned(min(f + NF * k, N1 - 1)) * slot_bytes);
+    }
+  };
+  StageTables<N, NF, BLOCK, PAIR> st;
   st.begin(args, 0, tid);
   const __amdgpu_buffer_rsrc_t rg = field_rsrc(args.g[f], field_bytes);
   float2 v[N1];
 #pragma unroll
   for (int e = 0; e < N1; ++e) v[e] = load_slot<false>(rg, lane_bytes, unsigned(e) * slot_bytes);
   float2 y[P][NF];
-#pragma unroll
-  for (int j = 0; j < NF; ++j) {
-    const __amdgpu_buffer_rsrc_t ry = field_rsrc(args.y[j], field_bytes);
-#pragma unroll
-    for (int k = 0; k < P; ++k)
-      y[k][j] = load_slot<false>(ry, lane_bytes, unsigned(min(f + NF * k, N1 - 1)) * slot_bytes);
-  }
-  st.end(false, tid, s_tw, s_prop, s_tw, s_prop);
+  load_points(args.y, y);
+  st.end(false, tid, s_tw, s_prop, s_tw2, s_prop2);
   __syncthreads();  // s_tw, s_prop staged
   LaneTwiddles<N1, N2, true> tw;
   tw.init(s_tw, t);
 
+  float2 gg[P][NF];
+  auto reverse_points = [&](float2 (&y)[P][NF], double (&dphi)[3]) {
+    dphi[0] = dphi[1] = dphi[2] = 0.0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      if (N1 % NF == 0 || f + NF * k < N1) {
+        // one point at a time: this point's values wait for the sums of the
+        // previous one (an empty asm, no instructions)
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+          asm volatile("" : "+v"(y[k][j].x), "+v"(y[k][j].y), "+v"(gg[k][j].x), "+v"(gg[k][j].y), "+v"(dphi[0]),
+                            "+v"(dphi[1]), "+v"(dphi[2]));
+        rk4_vjp_point<NF>(y[k], gg[k], co, sigma, dphi);
+      }
+    }
+  };
+  double dphi[3], dphi2[3];
   auto reverse_rk4 = [&]() {
     line_sync<WL>();   // this group's exchange rows are free
 #pragma unroll
     for (int e = 0; e < N1; ++e) mine[e * T + g] = v[e];
+    float2 yb[PAIR ? P : 1][NF];
+    if constexpr (PAIR) load_points(args.y2, yb);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       const int e = f + NF * k;
+#pragma unroll
+      for (int j = 0; j < NF; ++j)
+        gg[k][j] = (N1 % NF == 0 || e < N1) ? lds[j * XS + e * T + g] : make_float2(0.f, 0.f);
+    }
+    reverse_points(y, dphi);
+    if constexpr (PAIR) {
+      load_coefficients<NF>(args.nl2, co);
+      reverse_points(yb, dphi2);
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const int e = f + NF * k;
       if (N1 % NF == 0 || e < N1) {
-        float2 gg[NF];
 #pragma unroll
-        for (int j = 0; j < NF; ++j) gg[j] = lds[j * XS + e * T + g];
-        rk4_vjp_point<NF>(y[k], gg, co, sigma, dphi);
-#pragma unroll
-        for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = gg[j];
+        for (int j = 0; j < NF; ++j) lds[j * XS + e * T + g] = gg[k][j];
       }
     }
     __syncthreads();
@@ -327,26 +283,37 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass_spl
 
   if constexpr (AT == VJP_FIRST) reverse_rk4();
   line_trip<N1, N2, 1, WL, true>(v1, tw, t, lbuf, s_prop + f * N, K);
-  if constexpr (AT == VJP_LAST) reverse_rk4();
+  if constexpr (AT != VJP_FIRST) reverse_rk4();
+  if constexpr (PAIR) {
+    const DftConsts K2 = *args.consts2;
+    tw.init(s_tw2, t);
+    line_trip<N1, N2, 1, WL, true>(v1, tw, t, lbuf, s_prop2 + f * N, K2);
+  }
   if (la.valid) {
 #pragma unroll
     for (int e = 0; e < N1; ++e) store_slot<false>(rg, lane_bytes, unsigned(e) * slot_bytes, v[e]);
-  } else {
-    dphi[0] = dphi[1] = dphi[2] = 0.0;   // a line past the last one counts for nothing
+  } else {   // a line past the last one counts for nothing
+    dphi[0] = dphi[1] = dphi[2] = 0.0;
+    dphi2[0] = dphi2[1] = dphi2[2] = 0.0;
   }
   reduce_dphi<BLOCK, T>(dphi, s_red, args.dphi_out);
+  if constexpr (PAIR) {
+    __syncthreads();   // the sums are read
+    reduce_dphi<BLOCK, T>(dphi2, s_red, args.dphi_out2);
+  }
 }
 
 // Sum the per-block phase derivatives of a segment's adjoint passes (fixed
 // order).  Block (i, w) handles step i of the segment and pass w (0: the
-// reverse first half-step, 1: the reverse second half-step), whose launch had
-// nblocks[w] blocks and wrote parts[((i * 2 + w) * stride + b) * 3 + k];
-// out[6 i + 3 w + k] receives the sum over b (block size 256).
+// reverse first half-step, 1: the reverse second half-step), which wrote
+// parts[((i * 2 + w) * stride + b) * 3 + k] for its blocks b; out[6 i + 3 w +
+// k] receives the sum over b (block size 256).  The sweep's axes alternate:
+// nblocks[w] blocks in the segment's last step and every second one before.
 static __global__ void reduce_dphi_segment(const double* parts, int nblocks0, int nblocks1,
                                            int stride, double* out) {
   __shared__ double s[256];
   const int i = blockIdx.x, w = blockIdx.y;
-  const int nb = w == 0 ? nblocks0 : nblocks1;
+  const int nb = ((int(gridDim.x) - 1 - i + w) & 1) == 0 ? nblocks0 : nblocks1;
   const double* src = parts + (size_t(i) * 2 + w) * size_t(stride) * 3;
   for (int k = 0; k < 3; ++k) {
     double acc = 0.0;

@@ -52,13 +52,12 @@ void launch_group_long(int nl, const GroupGeom& g, hipStream_t st, const PassArg
 // Blocks of an adjoint pass over `lines` lines of length n along axis.
 inline int adjoint_blocks(int axis, long lines, int n) {
   const int n2 = kBlock / lines_per_block(n);
-  const bool split = narrow_launch(lines, n2) || values_per_lane(n) > 24;   // (together_split)
-  const int lpb = (split ? split_threads(n2, axis) : kBlock) / n2;
+  const int lpb = split_threads(n2, axis) / n2;
   return int((lines + lpb - 1) / lpb);
 }
 
 // One adjoint pass (conj-propagator transforms with the RK4 half-step's VJP)
-// along x or tau (VJP_FIRST / VJP_LAST of adjoint.hpp).
+// along x or tau (VJP_* of adjoint.hpp).
 template <int N1, int N2>
 void launch_adj_axis(int axis, int at, const brahms_plan_s& p, const AdjArgs& a);
 

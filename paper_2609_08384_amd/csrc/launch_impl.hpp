@@ -256,39 +256,27 @@ void launch_group_long(int nl, const GroupGeom& g, hipStream_t st, const PassArg
 template <int N1, int N2, int AX, int NF, int AT>
 void launch_adj(const brahms_plan_s& p, const AdjArgs& a) {
   const long lines = AX == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
-  // (the block counts are adjoint_blocks' in launch.hpp)
-  if constexpr (together_split<N1>()) {
-    if (!narrow_launch(lines, N2)) {
-      const dim3 grid(blocks_of(lines, LineGeom<N1, N2>::LPB));
-      AdjArgs b = a;
-      b.tile_mul = AX == AX_T ? tile_multiplier(grid.x) : 1u;
-      hipLaunchKernelGGL((adjoint_pass<N1, N2, AX, NF, AT>), grid, dim3(kBlock), 0, p.stream, b);
-      return;
-    }
-  }
   constexpr int T = split_threads(N2, AX);
-  hipLaunchKernelGGL((adjoint_pass_split<N1, N2, AX, NF, AT>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0,
-                     p.stream, a);
+  // (the block counts are adjoint_blocks' in launch.hpp)
+  hipLaunchKernelGGL((adjoint_pass<N1, N2, AX, NF, AT>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0, p.stream,
+                     a);
+}
+
+template <int N1, int N2, int AX, int NF>
+void launch_adj_at(int at, const brahms_plan_s& p, const AdjArgs& a) {
+  if (at == VJP_PAIR) launch_adj<N1, N2, AX, NF, VJP_PAIR>(p, a);
+  else if (at == VJP_FIRST) launch_adj<N1, N2, AX, NF, VJP_FIRST>(p, a);
+  else launch_adj<N1, N2, AX, NF, VJP_LAST>(p, a);
 }
 
 template <int N1, int N2>
 void launch_adj_axis(int axis, int at, const brahms_plan_s& p, const AdjArgs& a) {
   if (axis == AX_X) {
-    if (p.nf == 3) {
-      if (at == VJP_FIRST) launch_adj<N1, N2, AX_X, 3, VJP_FIRST>(p, a);
-      else launch_adj<N1, N2, AX_X, 3, VJP_LAST>(p, a);
-    } else {
-      if (at == VJP_FIRST) launch_adj<N1, N2, AX_X, 2, VJP_FIRST>(p, a);
-      else launch_adj<N1, N2, AX_X, 2, VJP_LAST>(p, a);
-    }
+    if (p.nf == 3) launch_adj_at<N1, N2, AX_X, 3>(at, p, a);
+    else launch_adj_at<N1, N2, AX_X, 2>(at, p, a);
   } else {
-    if (p.nf == 3) {
-      if (at == VJP_FIRST) launch_adj<N1, N2, AX_T, 3, VJP_FIRST>(p, a);
-      else launch_adj<N1, N2, AX_T, 3, VJP_LAST>(p, a);
-    } else {
-      if (at == VJP_FIRST) launch_adj<N1, N2, AX_T, 2, VJP_FIRST>(p, a);
-      else launch_adj<N1, N2, AX_T, 2, VJP_LAST>(p, a);
-    }
+    if (p.nf == 3) launch_adj_at<N1, N2, AX_T, 3>(at, p, a);
+    else launch_adj_at<N1, N2, AX_T, 2>(at, p, a);
   }
 }
 

@@ -67,7 +67,4 @@ inline int lines_per_block(int n, bool alt = false) {
   return 0;
 }
 
-// Values per lane of length n's first split.
-inline int values_per_lane(int n) { return n * lines_per_block(n) / 256; }
-
 }  // namespace brahms
