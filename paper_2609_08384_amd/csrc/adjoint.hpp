@@ -176,7 +176,8 @@ __device__ __forceinline__ void reduce_dphi(const double* dphi, double (*s_red)[
 // tau first 33.6 / 32.2 (three fields, tau first 46.9 / 66.3, the one form
 // that lost, but x last 65.7 / 44.6).  What bounds it: six field transfers,
 // 50 MB at 128 x 128 x 64, 10 us; the rest is the chain of two waves a SIMD.
-// A pair moves eight where two passes move twelve.
+// A pair moves eight where two passes move twelve: 29-30 us against 19 + 20
+// (beside the next segment's forward steps on the other stream).
 template <int N1, int N2, int AX, int NF, int AT>
 __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(AdjArgs args) {
   constexpr int T = split_threads(N2, AX), BLOCK = NF * T;
@@ -195,7 +196,8 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(Adj
   const int g = tid % T;
   const int t = AX == AX_X ? g % N2 : g / G::LPB;
   const int li = AX == AX_X ? g / N2 : g % G::LPB;
-  const LineAddr la = line_addr<AX, N>(args, blockIdx.x * unsigned(G::LPB) + unsigned(li));
+  const unsigned bx = AX == AX_X ? slab_tile(args, blockIdx.x) : blockIdx.x;
+  const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
   const unsigned idx0 = la.base + unsigned(t) * la.estride;
   const unsigned field_bytes = unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) * 8u;
   const unsigned lane_bytes = idx0 * 8u, slot_bytes = unsigned(N2) * la.estride * 8u;

@@ -4,14 +4,16 @@
 // the fields, and one workspace holding the axis twiddles, the integrated
 // mismatch profile, and a ring of per-step tables (propagators and RK4
 // coefficients) that a small kernel refills every kChunk steps.  A z-step is
-// three launches on the caller's stream, one per axis in the schedule's pass
-// order (e.g. X pass: RK4 half-step + x line transforms, Y pass: y line
-// transforms, T pass: tau line transforms + RK4 half-step); five launches
-// when the tau axis is longer than 256.  With merged half-steps one RK4 step
-// of size dz joins consecutive steps; with fused step pairs the steps
-// alternate their axis order and one launch ends a step and begins the next
-// (two launches per step, four with a long tau axis).  With the graph
-// schedule whole chunks are replayed from a hipGraph.
+// one pass per axis in the schedule's pass order (e.g. X pass: RK4 half-step +
+// x line transforms, Y pass: y line transforms, T pass: tau line transforms +
+// RK4 half-step); with literal half-steps the order alternates from step to
+// step, and the last pass of one step and the first one of the next are one
+// launch: two launches per step.  Five launches when the tau axis is longer
+// than 256.  With merged half-steps one RK4 step of size dz joins consecutive
+// steps: three launches per step, or two (four with a long tau axis) with
+// fused step pairs.  Plane waves (nx = ny = 1) run all the steps of a chunk
+// in one launch.  With the graph schedule whole chunks are replayed from a
+// hipGraph.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -1,7 +1,7 @@
 // Device kernels of the chi(2) split-step z-loop (gfx950).
 //
-// One z-step (symmetric splitting N/2 - L - N/2, Sec. 3.1 eq. expon) is three
-// HBM passes over the fields, each a batch of independent 1D lines:
+// One z-step (symmetric splitting N/2 - L - N/2, Sec. 3.1 eq. expon) is made
+// of three passes over the fields, each a batch of independent 1D lines:
 //
 //   X pass : RK4 half-step of the coupled chi(2) equations (eqs. CEp/CEs/CEi),
 //            then FFT_x . P_x . IFFT_x                    (all fields together)
@@ -16,7 +16,10 @@
 // the y and tau passes read their lines with a stride instead of
 // materialising the paper's reordered copy.  The passes may run in either
 // order (x, y, tau or tau, y, x); a tau axis longer than 256 takes three
-// passes (a four-step transform, AX_TAF / AX_TB / AX_TAI below).
+// passes (a four-step transform, AX_TAF / AX_TB / AX_TAI below).  Where two
+// consecutive steps meet along one axis, the one's T pass and the other's X
+// pass (or the other way round) are a single fused pass, NL_FUSE: two reads
+// and writes of the fields per step.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -366,9 +369,8 @@ __device__ __forceinline__ void line_trip(float2 (&v)[NF][N1], const LaneTwiddle
 // step-pair pass's LDS allows 3 blocks as well; without the bound the
 // compiler may take more registers and leave room for 2 waves only, which
 // cost the fused pass ~15 % of its speed.  Kernels whose LDS already limits
-// them to fewer blocks keep their register count.  Lines of 36 values per
-// lane (lengths 72 and 144) need 216 VGPRs for three fields and an LDS row
-// block that leaves room for one block per CU, so they are compiled for one.
+// them to fewer blocks keep their register count.  Lines of 18 and 24 values
+// per lane are compiled for two blocks, linear passes of 36 for one.
 #ifndef BRAHMS_MIN_BLOCKS
 #define BRAHMS_MIN_BLOCKS 3
 #endif
@@ -553,6 +555,23 @@ constexpr bool twiddle_registers() {
   return BLOCK > kBlock ? N1 <= 16 : N1 * NF <= 72;   // (short blocks as kBlock)
 }
 
+// Block -> tile map of the x and y passes: blocks go to the eight XCDs in turn,
+// and each XCD is given an eighth of the tiles in a row, a slab of tau planes.
+// An x pass and the y pass before or after it then work on the same slab in
+// the same XCD, whose L2 (4 MB) still holds it while the state is small: 64^3
+// and two fields, x, y, tau, y passes of a step pair: 27.0 -> 23.4 us; 96 x 96
+// x 64: 50.0 -> 44.9; 128 x 128 x 64: 61.2 -> 54.3; runs of 128^3 and three
+// fields (6 MB per XCD) 1753 -> 1678 us.  Not beyond 4M points a field, whose
+// slabs are several times the L2 (256^3: 5296 -> 5469 us on all its tiles), nor
+// with less than a plane per XCD (CW 128 x 128: 561 -> 579).  (tau lines cross
+// every slab.)
+template <class Args>
+__device__ __forceinline__ unsigned slab_tile(const Args& args, unsigned bx) {
+  if (args.nt < 8 || unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) > (1u << 22)) return bx;
+  const unsigned per_xcd = gridDim.x / 8u;
+  return bx < 8u * per_xcd ? bx % 8u * per_xcd + bx / 8u : bx;   // (the last few tiles as they come)
+}
+
 // bx: tile index along the launch's x dimension; field0: first field
 // handled (y pass: the block's field); next: a fused pass also applies the
 // next step's transform (false: the problem's last step, which ends on its
@@ -596,6 +615,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   // blocks are spread over the whole plane so that their strided rows fall
   // into many memory channels rather than one narrow address window
   if constexpr (AX == AX_T) bx = unsigned((unsigned long long)bx * args.tile_mul % args.tiles);
+  if constexpr (AX == AX_X || AX == AX_Y) bx = slab_tile(args, bx);
   const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
   const bool valid = la.valid;
   const unsigned lidx = la.lidx;
@@ -835,6 +855,7 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
   load_coefficients<NF>((NLM & NL_BEFORE) != 0 ? args.nl : args.nl2, co);
   const int t = AX == AX_X ? g % N2 : g / G::LPB;
   const int li = AX == AX_X ? g / N2 : g % G::LPB;
+  if constexpr (AX != AX_T) bx = slab_tile(args, bx);
   const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
   const unsigned idx0 = la.base + unsigned(t) * la.estride;
   const unsigned estep = unsigned(N2) * la.estride;
@@ -1045,7 +1066,8 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void axis_pass_split_
 // are spread over all the block's threads; a step's time is this serial chain
 // (no memory traffic to speak of), with the next step's tables loaded beside
 // it.  nt = 256, two fields, literal half-steps: 19.5 us a step as a launch
-// per step of one wave of 32 values a lane, 10.5 us with one field per wave.
+// per step of one wave of 32 values a lane, 10.5 us as a launch per step with
+// one field per wave, 4.0 us here.
 // ---------------------------------------------------------------------------
 template <int N1, int N2, int NF>
 __device__ __forceinline__ void line_steps_body(const PassArgs& args, int count, bool merged, bool first) {
