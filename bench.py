@@ -28,11 +28,12 @@ if ROOT not in sys.path:
 
 METRIC = "grid-point·z-steps/s + % HBM peak; adjoint/forward time; batched vs plain"
 HBM_PEAK_GBS = 8000.0
-# MI355X FP32 vector peak (published, with packed FP32 math) and the peak of
-# the unpacked FP32 instructions these kernels are built with: 256 CUs x 4
-# SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz
+# MI355X FP32 vector peak (published).  Unpacked instructions reach it: a SIMD
+# with two or more waves issues one wave64 FMA in 0.88-1.0 ns, two cycles
+# (256 CUs x 4 SIMDs x 32 lanes x 2 flops x 2.4 GHz).
 FP32_PEAK_TFLOPS = 157.3
-FP32_UNPACKED_TFLOPS = 78.6
+# passes that end one step and begin the next: their RK4 steps
+FUSED_MODES = {"fused": 1, "literal_pair": 2}
 
 
 def parse():
@@ -58,7 +59,7 @@ def parse():
     ap.add_argument("--literal-halves", action="store_true",
                     help="keep both RK4 half-steps of every step (no merging of adjacent halves)")
     ap.add_argument("--no-fuse", action="store_true",
-                    help="with a fixed pass order: three passes per step (no fused step pairs)")
+                    help="with a fixed pass order: merged steps of three passes (no fused step pairs)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="time a plain 1 GiB device-to-device copy instead (reference for "
                          "achievable bandwidth and for scaling hardware byte counters)")
@@ -370,8 +371,11 @@ def nl_of_pass(pass_order: int, merge_halves: int, fuse_steps: int = 0) -> dict:
     """RK4 mode of each pass in the steady state of a run: with merged
     half-steps the first pass of every step but the run's first is linear;
     with fused step pairs the first and last axes alternate as the pass that
-    ends one step and begins the next ("fused")."""
+    ends one step and begins the next ("fused"), and so they do with literal
+    half-steps ("literal_pair": both half-steps in that pass)."""
     modes = dict(NL_OF_PASS[pass_order])
+    if not merge_halves:
+        return {k: ("none" if v == "none" else "literal_pair") for k, v in modes.items()}
     if merge_halves and fuse_steps:
         return {k: ("none" if v == "none" else "fused") for k, v in modes.items()}
     if merge_halves:
@@ -379,16 +383,16 @@ def nl_of_pass(pass_order: int, merge_halves: int, fuse_steps: int = 0) -> dict:
     return modes
 
 
-def fused_pass_flops(nf: int, points: int, n_axis: int) -> float:
+def fused_pass_flops(nf: int, points: int, n_axis: int, rk4_steps: int = 1) -> float:
     """Algorithmic FP32 flops of one fused pass: per grid point and field two
     round trips along the axis (forward and inverse transform at the
     conventional 5 N log2 N flops each, and the 6-flop propagator product)
-    and one RK4 step of the coupled equations (per field four stages of one
+    and one RK4 step (two with literal half-steps) of the coupled equations (per field four stages of one
     complex product of two fields, 6 flops, the product with the stage
     coefficient, 6, the stage update, 2, and the weighted accumulation, 8)."""
     import math
     per_trip = 2 * 5 * math.log2(n_axis) + 6
-    return float(points) * nf * (2 * per_trip + 4 * (6 + 6 + 2 + 8))
+    return float(points) * nf * (2 * per_trip + rk4_steps * 4 * (6 + 6 + 2 + 8))
 
 
 def measured_traffic(workload: str, pass_name: str, pass_order: int, merge_halves: int = 0,
@@ -530,11 +534,10 @@ def main():
     for k, rec in per_kernel.items():
         if k in modes:
             rec["rk4"] = modes[k]
-            if modes[k] == "fused" and rec["launches"]:
+            if modes[k] in FUSED_MODES and rec["launches"]:
                 n_axis = {"x_pass": wl.nx, "y_pass": wl.ny, "t_pass": wl.nt}[k]
-                tf = fused_pass_flops(wl.nf, wl.points, n_axis) / (rec["avg_ms"] * 1e-3) / 1e12
+                tf = fused_pass_flops(wl.nf, wl.points, n_axis, FUSED_MODES[modes[k]]) / (rec["avg_ms"] * 1e-3) / 1e12
                 rec.update({"bound": "alu", "TFLOPs": round(tf, 2), "frac": round(tf / FP32_PEAK_TFLOPS, 4),
-                            "frac_of_unpacked_fp32_peak": round(tf / FP32_UNPACKED_TFLOPS, 4),
                             "hbm_frac": round(rec["GBps"] / HBM_PEAK_GBS, 4)})
             elif rec["GBps"]:
                 rec.update({"bound": "hbm", "frac": round(rec["GBps"] / HBM_PEAK_GBS, 4)})
@@ -542,7 +545,7 @@ def main():
     # time, the fused passes of the two alternating axes counted as one kind
     kinds = {}
     for k, (ms, n) in passes.items():
-        kind = "fused_pass" if modes.get(k) == "fused" else k
+        kind = "fused_pass" if modes.get(k) in FUSED_MODES else k
         t = kinds.setdefault(kind, [0.0, 0, []])
         t[0] += ms
         t[1] += n
@@ -553,11 +556,10 @@ def main():
     achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9
     if dom == "fused_pass":
         axis_len = {"x_pass": wl.nx, "y_pass": wl.ny, "t_pass": wl.nt}[dom_members[0]]
-        flops = fused_pass_flops(wl.nf, wl.points, axis_len)
+        flops = fused_pass_flops(wl.nf, wl.points, axis_len, FUSED_MODES[modes[dom_members[0]]])
         tflops = flops / (avg_ms * 1e-3) / 1e12
         dominant = {"kernel": dom, "axes": dom_members, "bound": "alu", "achieved": round(tflops, 2),
                     "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tflops / FP32_PEAK_TFLOPS, 4),
-                    "frac_of_unpacked_fp32_peak": round(tflops / FP32_UNPACKED_TFLOPS, 4),
                     "hbm_GBps": round(achieved, 1), "algorithmic_flops_per_launch": flops,
                     "avg_launch_ms": round(avg_ms, 5), "share_of_step_time": round(dom_ms / sum(
                         v[0] for v in passes.values()), 4)}
@@ -570,7 +572,8 @@ def main():
     # the timed region (so launch gaps count), with the summed pass durations
     # of the event-timed run beside it
     long_t = wl.nt > 256
-    p_step = (4 if long_t else 2) if (merge and fuse) else (5 if long_t else 3)
+    pairs = (merge and fuse) or (not merge and not long_t)
+    p_step = (4 if long_t else 2) if pairs else (5 if long_t else 3)
     step_bytes = p_step * bytes_per_launch
     timed_steps = max(1, tsteps)
     summed_ms = sum(v[0] for v in tim.values()) / timed_steps

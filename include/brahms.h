@@ -170,7 +170,12 @@ brahms_status brahms_plan_destroy(brahms_plan plan);
  * applied as three commuting one-axis operators (Sec. 3.1: the dispersion
  * and diffraction operators commute), each a pass over the fields; the first
  * pass of a z-step also performs the first Runge-Kutta half-step and the last
- * pass the second one.
+ * pass the second one.  With literal half-steps, steps of odd index (step
+ * index = round(z / dz), whatever call a step belongs to) take the axes below
+ * in reverse order, so that one step's second half-step and the next one's
+ * first half-step are along one axis and run as one pass within a call; the
+ * fields are the same bits however a run is cut into calls.  (Not for plane
+ * waves, whose steps are one pass, nor for a tau axis longer than 256.)
  *   pass_order 0: x pass, y pass, tau pass (default)
  *   pass_order 1: tau pass, y pass, x pass
  *   pass_order 2: x pass, tau pass, y pass (tau linear, one field per block)
@@ -196,7 +201,8 @@ brahms_status brahms_plan_destroy(brahms_plan plan);
  *     half-steps while monitor records or snapshots are set; the adjoint
  *     always differentiates the literal half-steps.
  *   fuse_steps 1 (needs merge_halves 1; not for nx = ny = 1 with tau <= 256,
- *     whose steps are one pass): within one call, even steps (counted from
+ *     whose steps are one pass, and without effect on merged steps of two
+ *     passes, nt = 1 without loss, which always run this way): within one call, even steps (counted from
  *     the call's first) take the axes in pass_order's order a, m, b and odd
  *     steps in the order b, m, a (a long tau axis is m, its three passes in
  *     the middle; x and y are a and b, y first for odd pass orders).  The axis operators commute (Sec. 3.1), so this
@@ -357,7 +363,8 @@ brahms_status brahms_adjoint(brahms_plan plan, int nsteps, int checkpoint_every,
  * brahms_batch_set_fuse_steps: 1 runs the launch groups whose steps take
  *   three passes as fused step pairs (as the plan schedule field fuse_steps;
  *   a problem's last step ends on its own second half-step inside the fused
- *   launch).  Needs merged half-steps (BRAHMS_E_INVALID_ARG otherwise);
+ *   launch).  Literal half-steps, and merged steps of two passes, run in pairs
+ *   either way, as they do in plans.  Needs merged half-steps (BRAHMS_E_INVALID_ARG otherwise);
  *   BRAHMS_E_UNSUPPORTED for a batch that holds a problem with a tau axis
  *   longer than 256.  Invalidates the binding.
  * brahms_batch_set_splits: per-problem register/lane splits (n entries, the
