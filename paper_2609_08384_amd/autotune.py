@@ -29,6 +29,10 @@ from . import brahms
 
 CANDIDATES = [{"pass_order": o, "graph": g} for g in (0, 1) for o in (0, 1, 2, 3)]
 ROUNDS = 3   # timing rounds per candidate (the best is kept)
+# Generation of the kernels that a cached choice was timed on, kept with each
+# entry of the disk cache: entries of another one, or of none, are timed again.
+# To be raised when the pass kernels or the rules that pick them change.
+KERNELS = 9
 _lock = threading.Lock()
 _memo: Dict[str, dict] = {}
 
@@ -44,8 +48,16 @@ def _arch(device) -> str:
     return getattr(props, "gcnArchName", "unknown").split(":")[0]
 
 
-def _key(arch: str, nx: int, ny: int, nt: int, nf: int, merge: int) -> str:
-    return f"v8:{arch}:{nx}x{ny}x{nt}:nf{nf}:m{merge}"
+def two_axes(nx: int, ny: int, nt: int, params: brahms.Params) -> bool:
+    """Whether a plan's steps have an x and a y pass only: nt = 1 with no loss
+    and no transverse map."""
+    return (nt == 1 and nx > 1 and ny > 1 and getattr(params, "dk_map", None) is None and
+            all(f.alpha == 0.0 for f in params.fields))
+
+
+def _key(arch: str, nx: int, ny: int, nt: int, nf: int, merge: int, three: bool = False) -> str:
+    """three: nt = 1, and steps of three passes all the same."""
+    return f"v8:{arch}:{nx}x{ny}x{nt}:nf{nf}:m{merge}" + (":p3" if three else "")
 
 
 def split_masks(nx: int, ny: int, nt: int):
@@ -59,13 +71,13 @@ def split_masks(nx: int, ny: int, nt: int):
     return masks
 
 
-def wide_masks(schedule: dict, nx: int, ny: int, nt: int):
+def wide_masks(schedule: dict, nx: int, ny: int, nt: int, two: bool = False):
     """Values of the schedule field `wide` worth timing: each axis whose
     passes are linear in this schedule (the middle axis; with merged
     half-steps and no fused pairs also the first), alone and together;
-    none for long tau axes, and none on axes of length 1 or of a length
-    without a wide form (brahms.NARROW_ONLY_LENGTHS)."""
-    if nt > 256:
+    none for long tau axes and steps of two axes (`two`), and none on axes of
+    length 1 or of a length without a wide form (brahms.NARROW_ONLY_LENGTHS)."""
+    if nt > 256 or two:
         return []
     order = [(0, 1, 2), (2, 1, 0), (0, 2, 1), (1, 2, 0)][schedule["pass_order"]]
     linear = [order[1]]
@@ -137,20 +149,26 @@ def tune(nx: int, ny: int, nt: int, nf: int, params: brahms.Params, device="cuda
     """Best schedule for this shape (cached in memory and on disk)."""
     arch = _arch(device)
     merge = int(merge_halves and can_merge(params))
-    key = _key(arch, nx, ny, nt, nf, merge)
+    two = two_axes(nx, ny, nt, params)
+    key = _key(arch, nx, ny, nt, nf, merge, three=nt == 1 and nx > 1 and ny > 1 and not two)
     with _lock:
         if not refresh:
             if key in _memo:
                 return _memo[key]
             disk = _load()
-            if key in disk:
+            if key in disk and disk[key].get("kernels") == KERNELS:
                 _memo[key] = disk[key]["schedule"]
                 return _memo[key]
         # time with the same linear coefficients but no coupling blow-up risk
         scratch = brahms.Params(dz=params.dz, fields=params.fields, dk_const=params.dk_const,
                                 dk=None, dx=params.dx, dy=params.dy, dt=params.dt)
-        fuses = (0, 1) if merge and can_fuse(nx, ny, nt) else (0,)
-        cands = [dict(c, merge_halves=merge, fuse_steps=f) for f in fuses for c in CANDIDATES]
+        if nt == 1:
+            scratch.dk_map = getattr(params, "dk_map", None)   # (it decides the passes of a step)
+        # steps of two axes run in pairs whatever fuse_steps says, and orders
+        # 2 and 3 are their orders 0 and 1
+        fuses = (0, 1) if merge and can_fuse(nx, ny, nt) and not two else (0,)
+        cands = [dict(c, merge_halves=merge, fuse_steps=f) for f in fuses for c in CANDIDATES
+                 if not (two and c["pass_order"] > 1)]
         # the candidates differ by a few per cent: a warm-up run brings the
         # clocks up first, and each candidate keeps the best of ROUNDS
         # interleaved rounds (a slow round on a throttled clock then hits
@@ -177,7 +195,7 @@ def tune(nx: int, ny: int, nt: int, nf: int, params: brahms.Params, device="cuda
                 best_ms, best = t, c
         # 512-thread blocks for the linear passes, on the axes whose passes
         # are linear in the best schedule
-        for mask in wide_masks(best, nx, ny, nt):
+        for mask in wide_masks(best, nx, ny, nt, two):
             c = dict(best, wide=mask)
             t = min(measure(nx, ny, nt, nf, scratch, c, device) for _ in range(ROUNDS))
             times.append((t, c))
@@ -185,7 +203,7 @@ def tune(nx: int, ny: int, nt: int, nf: int, params: brahms.Params, device="cuda
                 best_ms, best = t, c
         _memo[key] = dict(best)
         disk = _load()
-        disk[key] = {"schedule": dict(best), "ms_per_step": best_ms,
+        disk[key] = {"schedule": dict(best), "kernels": KERNELS, "ms_per_step": best_ms,
                      "candidates": [{"schedule": c, "ms_per_step": t} for t, c in times]}
         _store(disk)
         return _memo[key]
