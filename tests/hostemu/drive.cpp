@@ -535,6 +535,101 @@ void scenario_plans() {
   std::printf("plans: ok\n");
 }
 
+// A plan and its memory, for call sequences of the scenarios below.
+struct Solve {
+  brahms_plan plan = nullptr;
+  Fields f;
+  void* ws = nullptr;
+  Solve(Problem& p, const brahms_schedule& sc) {
+    set_profile(p);
+    std::vector<Problem> one{p};
+    f = upload(one);
+    OK(brahms_plan_create(p.nx, p.ny, p.nt, p.nf, &p.prm, nullptr, &plan));
+    size_t bytes = 0;
+    OK(brahms_plan_workspace_size(plan, &bytes));
+    ws = emu::device_alloc(bytes);
+    emu::clear_regions();
+    for (size_t k = 0; k < f.ptr.size(); ++k) emu::register_region(f.ptr[k], f.bytes[k], 0, "field");
+    emu::register_region(ws, bytes, 0, "plan workspace");
+    OK(brahms_plan_set_schedule(plan, &sc));
+    std::vector<void*> fp(f.ptr.begin(), f.ptr.end());
+    OK(brahms_plan_bind(plan, fp.data(), ws));
+  }
+  std::vector<std::vector<float2>> finish() {
+    OK(hipDeviceSynchronize() == hipSuccess ? BRAHMS_OK : BRAHMS_E_DEVICE);
+    std::vector<std::vector<float2>> out;
+    for (size_t k = 0; k < f.ptr.size(); ++k)
+      out.emplace_back(f.ptr[k], f.ptr[k] + f.bytes[k] / sizeof(float2));
+    OK(brahms_plan_destroy(plan));
+    emu::device_free(ws);
+    release(f);
+    emu::clear_regions();
+    return out;
+  }
+};
+
+std::vector<std::vector<float2>> run_calls(Problem& p, const brahms_schedule& sc, const std::vector<int>& calls) {
+  Solve s(p, sc);
+  for (int n : calls) OK(brahms_step(s.plan, n));
+  return s.finish();
+}
+
+brahms_schedule schedule(int order, int graph = 0, int merge = 0, int fuse = 0) {
+  brahms_schedule sc{};
+  sc.pass_order = order;
+  sc.graph = graph;
+  sc.merge_halves = merge;
+  sc.fuse_steps = fuse;
+  return sc;
+}
+
+// literal steps in pairs with a transverse map: the same bits in calls of any
+// length, two and three fields, the map on x and on tau ends
+void scenario_maps() {
+  Rng r(101);
+  for (int nf : {2, 3})
+    for (int order : {0, 1}) {
+      Problem p = make_problem(r, 12, 8, 16, nf, 70, nf == 2, 0.7);
+      std::vector<double> map(size_t(p.nx) * p.ny);
+      for (double& v : map) v = r.uniform(-2, 2);
+      p.prm.dk_map = map.data();
+      const auto whole = run_calls(p, schedule(order), {70});
+      expect_equal(whole, run_calls(p, schedule(order), {1, 2, 66, 1}), "map, calls of odd lengths");
+      expect_equal(whole, run_calls(p, schedule(order, 1), {70}), "map, graph replay");
+    }
+  std::printf("maps: ok\n");
+}
+
+// the adjoint: segments of one step and of several, the last one shorter, a
+// second stream's segment beside the sweep
+void scenario_adjoint() {
+  Rng r(109);
+  const int spec[3][4] = {{16, 6, 12, 2}, {9, 4, 16, 3}, {1, 1, 32, 2}};
+  for (auto& sp : spec)
+    for (int every : {1, 3}) {
+      Problem p = make_problem(r, sp[0], sp[1], sp[2], sp[3], 7, true, 0.0);
+      Solve s(p, schedule(every == 1 ? 1 : 0));
+      size_t bytes = 0;
+      OK(brahms_adjoint_workspace_size(s.plan, 7, every, &bytes));
+      void* aws = emu::device_alloc(bytes);
+      emu::register_region(aws, bytes, -1, "adjoint workspace");
+      std::vector<Problem> one{p};
+      Fields g = upload(one);
+      for (size_t k = 0; k < g.ptr.size(); ++k) emu::register_region(g.ptr[k], g.bytes[k], -1, "cotangent");
+      std::vector<void*> gp(g.ptr.begin(), g.ptr.end());
+      std::vector<double> dk(7, NAN);
+      OK(brahms_adjoint_forward(s.plan, 7, every, aws));
+      OK(brahms_adjoint_backward(s.plan, gp.data(), dk.data()));
+      OK(hipDeviceSynchronize() == hipSuccess ? BRAHMS_OK : BRAHMS_E_DEVICE);
+      for (double v : dk)
+        if (!std::isfinite(v)) emu::die("adjoint: dk gradient not finite");
+      emu::device_free(aws);
+      release(g);
+      s.finish();
+    }
+  std::printf("adjoint: ok\n");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -554,6 +649,8 @@ int main(int argc, char** argv) {
   else if (s == "three_lengths") scenario_three_lengths();
   else if (s == "stream_graphs") scenario_stream_graphs();
   else if (s == "splits") scenario_splits();
+  else if (s == "maps") scenario_maps();
+  else if (s == "adjoint") scenario_adjoint();
   else {
     std::fprintf(stderr, "unknown scenario %s\n", s.c_str());
     return 2;

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "emu.hpp"
+#include "adjoint.hpp"
 #include "kernels.hpp"
 
 emu_uint3 threadIdx, blockIdx, blockDim, gridDim;
@@ -330,8 +331,10 @@ void check_pass(const brahms::PassArgs& a, int nf, const std::string& what) {
   for (int j = 0; j < nf; ++j)
     table(a.prop + size_t(j) * a.field_stride + a.axis_off, size_t(n), "propagator");
   same_owner(owner, owner_of(a.consts, sizeof(brahms::DftConsts), what + " consts"), what);
-  table(a.nl, size_t(nf) * brahms::kNlCoef, "rk4 coefficients");
-  table(a.nl2, size_t(nf) * brahms::kNlCoef, "rk4 coefficients 2");
+  if (a.nl != nullptr || a.nl2 != nullptr) {   // (the adjoint's linear passes have none)
+    table(a.nl, size_t(nf) * brahms::kNlCoef, "rk4 coefficients");
+    table(a.nl2, size_t(nf) * brahms::kNlCoef, "rk4 coefficients 2");
+  }
   if (a.tw2 != nullptr) {
     table(a.tw2, size_t(n), "next twiddles");
     for (int j = 0; j < nf; ++j)
@@ -339,6 +342,7 @@ void check_pass(const brahms::PassArgs& a, int nf, const std::string& what) {
     same_owner(owner, owner_of(a.consts2, sizeof(brahms::DftConsts), what + " next consts"), what);
   }
   if (a.map != nullptr) table(a.map, size_t(3) * size_t(plane), "map factors");
+  if (a.map2 != nullptr) table(a.map2, size_t(3) * size_t(plane), "next map factors");
   if (a.tiles == 0 || a.tile_mul == 0) die(what + ": tile map with zero tiles");
 }
 
@@ -357,11 +361,82 @@ void check_tables(const brahms::TableArgs& t, const std::string& what) {
   }
 }
 
-long long g_checked_passes = 0, g_checked_tables = 0;
+// The ranges of `count` steps of a plane wave: its line, and the tables of
+// count consecutive rows (see line_steps_body).
+void check_line(const brahms::PassArgs& first, int nf, int count, const std::string& what) {
+  if (first.nx != 1 || first.ny != 1 || first.axis_off != 2) die(what + ": not a plane wave's tau pass");
+  if (count < 1) die(what + ": no steps");
+  const int row = brahms::table_row_stride(nf, 1, 1, first.nt);
+  brahms::PassArgs a = first;
+  a.tiles = a.tile_mul = 1;   // (not read)
+  for (int s = 0; s < count; ++s) {
+    check_pass(a, nf, what + ", step " + std::to_string(s));
+    a.tw += row;
+    a.prop += row;
+    a.consts = reinterpret_cast<const brahms::DftConsts*>(reinterpret_cast<const float2*>(a.consts) + row);
+    a.nl += 2 * nf * brahms::kNlCoef;
+    a.nl2 += 2 * nf * brahms::kNlCoef;
+  }
+}
+
+// The ranges one adjoint pass reads and writes (see AdjArgs).
+void check_adjoint(dim3 grid, const brahms::AdjArgs& a) {
+  const std::string what = "adjoint pass";
+  const size_t field_bytes = sizeof(float2) * size_t(a.nx) * a.ny * a.nt;
+  const int n = a.axis_off == 0 ? a.nx : a.nt;
+  if (a.axis_off != 0 && a.axis_off != a.nx + a.ny) die(what + ": axis_off names neither x nor tau");
+  int nf = 0;
+  while (nf < 3 && a.g[nf] != nullptr) ++nf;
+  auto half = [&](const float2* const* y, const float2* tw, const float2* prop, const float2* nl,
+                  const brahms::DftConsts* consts, const double* dphi) {
+    for (int j = 0; j < nf; ++j) {
+      owner_of(y[j], field_bytes, what + " saved state");
+      owner_of(prop + size_t(j) * a.field_stride + a.axis_off, sizeof(float2) * size_t(n), what + " propagator");
+    }
+    owner_of(tw, sizeof(float2) * size_t(n), what + " twiddles");
+    owner_of(nl, sizeof(float2) * size_t(nf) * brahms::kNlCoef, what + " rk4 coefficients");
+    owner_of(consts, sizeof(brahms::DftConsts), what + " consts");
+    owner_of(dphi, sizeof(double) * 3 * grid.x, what + " phase sums");
+  };
+  for (int j = 0; j < nf; ++j) owner_of(a.g[j], field_bytes, what + " cotangent");
+  half(a.y, a.tw, a.prop, a.nl, a.consts, a.dphi_out);
+  if (a.tw2 != nullptr) half(a.y2, a.tw2, a.prop2, a.nl2, a.consts2, a.dphi_out2);
+}
+
+long long g_checked_passes = 0, g_checked_tables = 0, g_graph_launches = 0;
+std::string g_axes;
+
+void check_args(dim3, const brahms::PassArgs& a, const int& count, const int&, const int&) {
+  int nf = 0;
+  while (nf < 3 && a.f[nf] != nullptr) ++nf;
+  check_line(a, nf, count, "plane wave");
+  ++g_checked_passes;
+}
+
+void check_args(dim3 grid, const brahms::PassArgs* const& descs, const long long& step, const int& count,
+                const int&) {
+  owner_of(descs, sizeof(brahms::PassArgs) * grid.x, "batched plane wave descriptors");
+  for (unsigned i = 0; i < grid.x; ++i) {
+    const brahms::PassArgs& a = descs[i];
+    if (step >= a.nz) continue;
+    int nf = 0;
+    while (nf < 3 && a.f[nf] != nullptr) ++nf;
+    const long long left = a.nz - step;
+    check_line(a, nf, left < count ? int(left) : count, "batched plane wave, instance " + std::to_string(i));
+    ++g_checked_passes;
+  }
+}
+
+void check_args(dim3 grid, const brahms::AdjArgs& a) {
+  check_adjoint(grid, a);
+  ++g_checked_passes;
+}
 
 void check_args(dim3 grid, const brahms::PassArgs& a) {
   int nf = 0;
   while (nf < 3 && a.f[nf] != nullptr) ++nf;
+  const char ax = a.axis_off == 0 ? 'x' : (a.axis_off == a.nx ? 'y' : 't');
+  g_axes += ax;
   // a linear pass of one field per block takes its field from blockIdx.z
   if (grid.z > 1 && int(grid.z) != nf) die("plain pass: gridDim.z is not the field count");
   check_pass(a, nf, "plain pass");
@@ -579,6 +654,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t exec, hipStream_t st) {
   if (exec == nullptr || !exec->alive) die("hipGraphLaunch of a destroyed graph exec");
   emu_stream* s = S(st, "hipGraphLaunch");
   if (s->cap) die("hipGraphLaunch into a capture");
+  ++emu::g_graph_launches;
   ++exec->pending;
   enqueue(s, [exec]() {
     if (!exec->alive) die("a graph exec was destroyed before its launch ran");

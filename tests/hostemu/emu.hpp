@@ -19,6 +19,9 @@ void device_free(void* p);
 void register_region(const void* p, size_t bytes, int owner, const char* what);
 void clear_regions();
 
-extern long long g_launches, g_checked_passes, g_checked_tables;
+extern long long g_launches, g_checked_passes, g_checked_tables, g_graph_launches;
+
+// The axes (x, y, t) of the plain passes run since it was last cleared.
+extern std::string g_axes;
 
 }  // namespace emu

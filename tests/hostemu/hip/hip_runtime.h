@@ -187,6 +187,7 @@ hipError_t hipGetSymbolAddress(void** ptr, const void* symbol);
 namespace brahms {
 struct PassArgs;
 struct TableArgs;
+struct AdjArgs;
 }  // namespace brahms
 
 namespace emu {
@@ -207,9 +208,20 @@ void check_args(dim3 grid, const brahms::PassArgs& a);
 void check_args(dim3 grid, const brahms::PassArgs* const& descs, const long long& step, const int& nf);
 void check_args(dim3 grid, const brahms::TableArgs& a);
 void check_args(dim3 grid, const brahms::TableArgs* const& targs);
+// plane waves: `count` steps from the tables of consecutive rows
+void check_args(dim3 grid, const brahms::PassArgs& a, const int& count, const int& merged, const int& first);
+void check_args(dim3 grid, const brahms::PassArgs* const& descs, const long long& step, const int& count,
+                const int& merged);
+void check_args(dim3 grid, const brahms::AdjArgs& a);
+
+// The arguments are taken by value when the launch is made (the caller's
+// variables may be gone when the stream reaches it).
+template <typename K, typename... A>
+inline void launch_args(hipStream_t s, dim3 grid, dim3 block, int site, K kernel, A... a) {
+  launch(s, grid, block, site, [=]() { kernel(a...); }, [=](dim3 g) { check_args(g, a...); });
+}
 
 }  // namespace emu
 
-#define hipLaunchKernelGGL(K, G, B, SHMEM, ST, ...)                                     \
-  ::emu::launch((ST), dim3(G), dim3(B), __LINE__, [=]() { K(__VA_ARGS__); },            \
-                [=](dim3 grid_) { ::emu::check_args(grid_, __VA_ARGS__); })
+#define hipLaunchKernelGGL(K, G, B, SHMEM, ST, ...) \
+  ::emu::launch_args((ST), dim3(G), dim3(B), __LINE__, [](auto... a_) { K(a_...); }, __VA_ARGS__)
