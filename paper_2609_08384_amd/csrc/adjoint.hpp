@@ -21,8 +21,6 @@
 
 namespace brahms {
 
-__device__ inline float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
-
 // g_y of the products Q (see chi2_products) for cotangent gq of Q.
 template <int NF>
 __device__ inline void chi2_products_vjp(const float2* y, const float2* gq, float2* gy) {

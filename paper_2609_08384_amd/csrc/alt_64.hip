@@ -1,5 +1,5 @@
-// Pass launchers of plans, batches and the adjoint for the second splits 16x4
+// Pass launchers of plans and batches for the second splits 16x4
 // (N1 x N2; see launch.hpp and lengths.hpp).
 #include "launch_impl.hpp"
 
-BRAHMS_INSTANTIATE_LENGTH(16, 4)
+BRAHMS_INSTANTIATE_PASSES(16, 4)

@@ -589,8 +589,8 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   constexpr bool REG = twiddle_registers<N1, NF, BLOCK>();
   // x lines: a line's N2 lanes are consecutive threads, within one wavefront
   constexpr bool WL = AX == AX_X && N2 <= 64 && 64 % N2 == 0;
-  static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)),
-                "the transverse map runs only with a half-step per pass on x or tau");
+  static_assert(NLM != NL_BOTH, "one line: axis_pass_split");
+  static_assert(!(MAP && AX == AX_Y), "the transverse map runs only on x or tau");
   constexpr bool LIT = (NL & NL_LIT) != 0;     // two half-steps between the transforms
   static_assert(!FUSE || (NLM == NL_AFTER && !(MAP && !LIT) && !LONG),
                 "a fused step pair ends one step and begins the next on one short axis");
@@ -841,7 +841,8 @@ __device__ __forceinline__ void axis_pass_split_body(const PassArgs& args, unsig
   constexpr bool WL = AX == AX_X && T == 64 && N2 <= 64 && 64 % N2 == 0;
   static_assert(NLM != NL_NONE && !long_tau_kind(AX) && T % 64 == 0, "a pass with an RK4 step on one line axis");
   constexpr bool LIT = (NL & NL_LIT) != 0;
-  static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)), "as in axis_pass_body");
+  static_assert(!(MAP && (NLM == NL_BOTH || AX == AX_Y)),
+                "the transverse map runs only with a half-step per pass on x or tau");
   // a group's LDS: its lines' exchange rows, or its values around the RK4 step
   constexpr int XS = N2 > 1 ? G::LDS_ELEMS : N1 * T;
   static_assert(XS >= N1 * T, "the exchange rows hold the group's values");

@@ -38,6 +38,12 @@ void launch_linear(bool wide, long lines, int nf, hipStream_t st, PassArgs a) {
   hipLaunchKernelGGL((axis_pass<N1, N2, AX, 1, NL_NONE>), grid, dim3(kBlock), 0, st, a);
 }
 
+template <int N1, int N2, int AX, int NF, int NL>
+void launch_split(long lines, hipStream_t st, const PassArgs& a) {
+  constexpr int T = split_threads(N2, AX);
+  hipLaunchKernelGGL((axis_pass_split<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0, st, a);
+}
+
 // A pass with an RK4 step: the fields together in a thread, or one field per
 // thread where the launch would leave SIMDs idle (narrow_launch; the same
 // bits either way).
@@ -50,8 +56,7 @@ void launch_rk4(long lines, hipStream_t st, const PassArgs& a) {
       return;
     }
   }
-  constexpr int T = split_threads(N2, AX);
-  hipLaunchKernelGGL((axis_pass_split<N1, N2, AX, NF, NL>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0, st, a);
+  launch_split<N1, N2, AX, NF, NL>(lines, st, a);
 }
 
 // Half-step modes of x, y and tau passes: the transverse map runs on x and
@@ -66,7 +71,7 @@ void launch_nl_nf(int nl, long lines, hipStream_t st, const PassArgs& a) {
       return launch_rk4<N1, N2, AX, NF, NL_AFTER | NL_FUSE | NL_LIT | NL_MAP>(lines, st, a);
   }
   if constexpr (AX == AX_T) {
-    if (nl == NL_BOTH) return launch_rk4<N1, N2, AX, NF, NL_BOTH>(lines, st, a);
+    if (nl == NL_BOTH) return launch_split<N1, N2, AX, NF, NL_BOTH>(lines, st, a);   // (one line)
   }
   if constexpr (AX != AX_Y) {
     if (nl == (NL_BEFORE | NL_MAP)) return launch_rk4<N1, N2, AX, NF, NL_BEFORE | NL_MAP>(lines, st, a);
@@ -283,8 +288,9 @@ void launch_adj_axis(int axis, int at, const brahms_plan_s& p, const AdjArgs& a)
 }  // namespace detail
 }  // namespace brahms
 
-// Explicit instantiations of the launchers of one line length.
-#define BRAHMS_INSTANTIATE_LENGTH(N1, N2)                                                              \
+// Explicit instantiations of the launchers of one line length (the adjoint
+// takes the first split of a length only).
+#define BRAHMS_INSTANTIATE_PASSES(N1, N2)                                                              \
   template hipError_t brahms::detail::launch_axis<N1, N2>(int, int, int, const brahms_plan_s&,        \
                                                           brahms::PassArgs);                           \
   template void brahms::detail::launch_group_pass<N1, N2>(int, int, const brahms::detail::GroupGeom&, \
@@ -295,7 +301,10 @@ void launch_adj_axis(int axis, int at, const brahms_plan_s& p, const AdjArgs& a)
                                                                 bool);                                \
   template void brahms::detail::launch_group_line_steps<N1, N2>(int, unsigned, hipStream_t,           \
                                                                 const brahms::PassArgs*, long long,   \
-                                                                int, bool);                           \
+                                                                int, bool);
+
+#define BRAHMS_INSTANTIATE_LENGTH(N1, N2)                                                              \
+  BRAHMS_INSTANTIATE_PASSES(N1, N2)                                                                    \
   template void brahms::detail::launch_adj_axis<N1, N2>(int, int, const brahms_plan_s&,               \
                                                         const brahms::AdjArgs&);
 
