@@ -365,7 +365,9 @@ __device__ __forceinline__ void line_trip(float2 (&v)[NF][N1], const LaneTwiddle
 #endif
 // Blocks of kBlock threads per CU the pass kernels are compiled for: 3 is
 // 3 waves per SIMD, a budget of 168 VGPRs (granules of 8 out of 512).  The
-// three-field passes that carry an RK4 step take 132-148 and the fused
+// three-field passes that carry an RK4 step take 162-168 with 16 values a
+// lane (a batch's keep one or two values in scratch memory, those of 24
+// values up to six) and the fused
 // step-pair pass's LDS allows 3 blocks as well; without the bound the
 // compiler may take more registers and leave room for 2 waves only, which
 // cost the fused pass ~15 % of its speed.  Kernels whose LDS already limits
@@ -415,19 +417,15 @@ __device__ inline void store_slot(__amdgpu_buffer_rsrc_t r, unsigned lane_bytes,
   __builtin_amdgcn_raw_buffer_store_b64(w, r, lane_bytes, slot_bytes, NT ? 2 : 0);
 }
 
-// Transverse phase factors of slot e at the half-step's three stage
-// positions: read per slot along x, the column's values along tau.
-template <int AX, int N2>
-__device__ __forceinline__ void map_factors(const float2* map, unsigned plane, unsigned xy0, int e,
-                                            const float2* wt, float2* w) {
-  if constexpr (AX == AX_T || long_tau_kind(AX)) {
+// Transverse phase factors at a half-step's three stage positions for the
+// (x, y) at the lane's byte offset plus the uniform slot_bytes, through a
+// buffer resource as the fields are: with 64-bit addresses of its own each of
+// the three factors of every slot along x takes two registers, and with three
+// fields 44-58 of a lane's values went to scratch memory.
+__device__ __forceinline__ void map_factors(__amdgpu_buffer_rsrc_t map, unsigned plane, unsigned lane_bytes,
+                                            unsigned slot_bytes, float2* w) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) w[k] = wt[k];
-  } else {
-    const unsigned xy = xy0 + unsigned(N2 * e);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) w[k] = map[k * plane + xy];
-  }
+  for (int k = 0; k < 3; ++k) w[k] = load_slot<false>(map, lane_bytes, unsigned(k) * plane * 8u + slot_bytes);
 }
 
 // ---------------------------------------------------------------------------
@@ -628,21 +626,11 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   }
   const unsigned idx0 = la.base + unsigned(t) * la.estride;
   const unsigned estep = unsigned(N2) * la.estride;
-  // transverse-map index of slot 0 (x pass: slot e adds N2 e; tau pass: the
-  // same column for every slot, so its three factors are read once here)
-  unsigned plane = 0, xy0 = 0;
-  float2 wt[3], wt2[3];
-  if constexpr (MAP) {
-    plane = unsigned(args.nx) * unsigned(args.ny);
-    xy0 = idx0 % plane;
-    if constexpr (AX == AX_T || LONG) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        wt[k] = args.map[k * plane + xy0];
-        if constexpr (LIT) wt2[k] = args.map2[k * plane + xy0];
-      }
-    }
-  }
+  // transverse-map offset of slot 0 (x pass: slot e adds N2 e entries; tau
+  // pass: the same column for every slot, its three factors are read once)
+  constexpr bool COLUMN = AX == AX_T || LONG;
+  const unsigned plane = unsigned(args.nx) * unsigned(args.ny);
+  const unsigned map_bytes = MAP ? (idx0 % plane) * 8u : 0u;
   // a line's LDS row (lines of one lane exchange nothing: no row)
   float2* lbuf = (N2 > 1) ? lds + li * G::LSTRIDE : lds;
   const DftConsts K = *args.consts;
@@ -717,8 +705,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
       for (int j = 0; j < NF; ++j) y[j] = v[j][e];
       if (e > 0) point_link<NF>(y, v, e - 1);
       if constexpr (MAP) {
-        float2 w[3];
-        map_factors<AX, N2>(args.map, plane, xy0, e, wt, w);
+        if constexpr (!COLUMN) map_factors(rmap, plane, map_bytes, unsigned(N2 * e) * 8u, w);
         rk4_point<NF, true>(y, co, w);
       } else {
         rk4_point<NF>(y, co);
@@ -745,6 +732,12 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
           v[j][e] = cmul(v[j][e], factor(t + N2 * e));
       } else if constexpr (AX == AX_TAI) {
         // conjugate twiddle, then the inverse B-point transform
+    __amdgpu_buffer_rsrc_t rmap;
+    float2 w[3];
+    if constexpr (MAP) {
+      rmap = field_rsrc(args.map, 3u * plane * 8u);
+      if constexpr (COLUMN) map_factors(rmap, plane, map_bytes, 0u, w);
+    }
 #pragma unroll
         for (int e = 0; e < N1; ++e)
           v[j][e] = cmulc(v[j][e], factor(t + N2 * e));
@@ -762,7 +755,10 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   }
 
   if constexpr ((NLM & NL_AFTER) != 0) {
-    if constexpr (NLM == NL_BOTH) load_coefficients<NF>(args.nl2, co);
+    // with a map, lines past the last one are done (nothing after this waits
+    // for them): were they to go on to the stores, the compiler would move the
+    // points' arithmetic down to the valid lines' stores, away from its factors
+    if (MAP && !FUSE && !valid) return;
     // (only unfused steps are asked for their values before the half-step)
     if (!FUSE && args.pre[0] != nullptr && valid) {
 #pragma unroll
@@ -772,7 +768,13 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
         for (int e = 0; e < N1; ++e) store_slot<NT>(rp, lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
       }
     }
-    auto half_step = [&](const float2* map, const float2* wcol) {
+    auto half_step = [&](const float2* map) {
+    __amdgpu_buffer_rsrc_t rmap;
+    float2 w[3];
+    if constexpr (MAP) {
+      rmap = field_rsrc(map, 3u * plane * 8u);
+      if constexpr (COLUMN) map_factors(rmap, plane, map_bytes, 0u, w);
+    }
 #pragma unroll
     for (int e = 0; e < N1; ++e) {
       float2 y[NF];
@@ -787,8 +789,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (MAP) {
-        float2 w[3];
-        map_factors<AX, N2>(map, plane, xy0, e, wcol, w);
+        if constexpr (!COLUMN) map_factors(rmap, plane, map_bytes, unsigned(N2 * e) * 8u, w);
         rk4_point<NF, true>(y, co, w);
       } else {
         rk4_point<NF>(y, co);
@@ -797,11 +798,11 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
       for (int j = 0; j < NF; ++j) v[j][e] = y[j];
     }
     };
-    half_step(args.map, wt);
+    half_step(args.map);
     if constexpr (FUSE) if (next) {
       if constexpr (LIT) {
         load_coefficients<NF>(args.nl, co);
-        half_step(args.map2, wt2);
+        half_step(args.map2);
       }
       // the next step's first transform along this axis
       __builtin_amdgcn_sched_barrier(0);

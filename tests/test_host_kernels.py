@@ -1,6 +1,6 @@
 """The kernels of the built library, from the metadata that the compiler puts
-beside their code: whether the kernels built are those that a dispatch can
-reach."""
+beside their code: how many bytes of scratch memory a lane takes, and whether
+the kernels built are those that a dispatch can reach."""
 import os
 import re
 import struct
@@ -65,6 +65,17 @@ def kernels():
             out[name, args] = k
     assert len(out) > 1000
     return out
+
+
+# bytes of scratch memory a lane may take: eight registers
+SCRATCH = 32
+
+
+@pytest.mark.parametrize("family", ["axis_pass", "axis_pass_split", "axis_pass_split_batched", "line_steps", "line_steps_batched"])
+def test_passes_keep_their_values_in_registers(kernels, family):
+    mine = {args: k[".private_segment_fixed_size"] for (name, args), k in kernels.items() if name == family}
+    assert mine
+    assert not {args: size for args, size in mine.items() if size > SCRATCH}
 
 
 def test_no_kernel_without_a_dispatch(kernels):
