@@ -698,6 +698,12 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
   tw.init(s_tw, t);
 
   if constexpr ((NLM & NL_BEFORE) != 0) {
+    __amdgpu_buffer_rsrc_t rmap;
+    float2 w[3];
+    if constexpr (MAP) {
+      rmap = field_rsrc(args.map, 3u * plane * 8u);
+      if constexpr (COLUMN) map_factors(rmap, plane, map_bytes, 0u, w);
+    }
 #pragma unroll
     for (int e = 0; e < N1; ++e) {
       float2 y[NF];
@@ -732,12 +738,6 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
           v[j][e] = cmul(v[j][e], factor(t + N2 * e));
       } else if constexpr (AX == AX_TAI) {
         // conjugate twiddle, then the inverse B-point transform
-    __amdgpu_buffer_rsrc_t rmap;
-    float2 w[3];
-    if constexpr (MAP) {
-      rmap = field_rsrc(args.map, 3u * plane * 8u);
-      if constexpr (COLUMN) map_factors(rmap, plane, map_bytes, 0u, w);
-    }
 #pragma unroll
         for (int e = 0; e < N1; ++e)
           v[j][e] = cmulc(v[j][e], factor(t + N2 * e));
