@@ -547,6 +547,27 @@ __device__ __forceinline__ void load_coefficients(const float2* nl, float2 (&co)
     for (int c = 0; c < kNlCoef; ++c) co[j][c] = wave_uniform(nl[j * kNlCoef + c]);
 }
 
+// The next step's DftConsts, read behind the pass's first barrier, where a
+// batch's descriptor is no longer known to be the same in every lane and 16
+// vector registers would hold them through the transforms.  SCALAR (three
+// fields of a batch where the registers are short: 16 values a lane, or 192 and
+// two half-steps): moved into scalar registers, else those pairs keep 8-39
+// values of a lane in scratch memory (now 6 at most; 64 x 256 x 256, literal:
+// 3254 -> 3207 us a run).  Elsewhere there is room and the wait for them costs
+// 1-2 % (192 x 64 x 64, merged: 2100 / 2123 us).
+template <bool SCALAR>
+__device__ __forceinline__ DftConsts next_consts(const DftConsts* p) {
+  if constexpr (!SCALAR) return *p;
+  union {
+    float2 w[sizeof(DftConsts) / sizeof(float2)];
+    DftConsts k;
+  } u;
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(u.w) / sizeof(float2); ++i)
+    u.w[i] = wave_uniform(reinterpret_cast<const float2*>(p)[i]);
+  return u.k;
+}
+
 // Whether a lane's twiddles stay in registers: where its values leave room.
 template <int N1, int NF, int BLOCK>
 constexpr bool twiddle_registers() {
@@ -573,8 +594,8 @@ __device__ __forceinline__ unsigned slab_tile(const Args& args, unsigned bx) {
 // bx: tile index along the launch's x dimension; field0: first field
 // handled (y pass: the block's field); next: a fused pass also applies the
 // next step's transform (false: the problem's last step, which ends on its
-// own second half-step).
-template <int N1, int N2, int AX, int NF, int NL, int BLOCK = kBlock>
+// own second half-step).  BATCH: args is a descriptor in memory.
+template <int N1, int N2, int AX, int NF, int NL, int BLOCK = kBlock, bool BATCH = false>
 __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx, int field0,
                                                bool next = true) {
   using G = LineGeom<N1, N2, BLOCK>;
@@ -806,7 +827,8 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
       }
       // the next step's first transform along this axis
       __builtin_amdgcn_sched_barrier(0);
-      const DftConsts K2 = *args.consts2;
+      const DftConsts K2 =
+          next_consts<BATCH && NF == 3 && (N1 == 16 || (N1 * N2 == 192 && LIT))>(args.consts2);
       LaneTwiddles<N1, N2, REG> tw2;
       tw2.init(s_tw2, t);
       line_trip<N1, N2, NF, WL, false>(v, tw2, t, lbuf, s_prop2, K2);
@@ -1040,8 +1062,8 @@ __global__ __launch_bounds__(BLOCK, (pass_min_blocks<N1, N2, BLOCK>())) void axi
   const PassArgs& a = descs[inst];
   if (step >= a.nz) return;
   // a fused pass ends the problem's last step without the next transform
-  axis_pass_body<N1, N2, AX, NF, NL, BLOCK>(a, blockIdx.x, per_field ? int(blockIdx.z % unsigned(nf)) : 0,
-                                            step + 1 < a.nz);
+  axis_pass_body<N1, N2, AX, NF, NL, BLOCK, true>(a, blockIdx.x, per_field ? int(blockIdx.z % unsigned(nf)) : 0,
+                                                  step + 1 < a.nz);
 }
 
 // The passes with one field per thread, of one problem and of a group.
