@@ -183,6 +183,10 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(Adj
   constexpr int N = G::N;
   constexpr bool WL = AX == AX_X && T == 64 && N2 <= 64 && 64 % N2 == 0;
   constexpr bool PAIR = AT == VJP_PAIR;
+  // blocks of more than two waves per SIMD (three fields, 16 lanes on tau)
+  // have 168 registers a lane: twiddles from LDS, and a pair's second states
+  // loaded behind the first reverse RK4 rather than ahead of it
+  constexpr bool TIGHT = BLOCK > 512;
   static_assert(AX == AX_X || AX == AX_T, "RK4 reverse sweeps live in the x or tau pass");
   constexpr int XS = N2 > 1 ? G::LDS_ELEMS : N1 * T;
   __shared__ float2 lds[NF * XS];
@@ -228,7 +232,7 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(Adj
   load_points(args.y, y);
   st.end(false, tid, s_tw, s_prop, s_tw2, s_prop2);
   __syncthreads();  // s_tw, s_prop staged
-  LaneTwiddles<N1, N2, true> tw;
+  LaneTwiddles<N1, N2, !TIGHT> tw;
   tw.init(s_tw, t);
 
   float2 gg[P][NF];
@@ -253,7 +257,7 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(Adj
 #pragma unroll
     for (int e = 0; e < N1; ++e) mine[e * T + g] = v[e];
     float2 yb[PAIR ? P : 1][NF];
-    if constexpr (PAIR) load_points(args.y2, yb);
+    if constexpr (PAIR && !TIGHT) load_points(args.y2, yb);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < P; ++k) {
@@ -264,6 +268,10 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(Adj
     }
     reverse_points(y, dphi);
     if constexpr (PAIR) {
+      if constexpr (TIGHT) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_points(args.y2, yb);
+      }
       load_coefficients<NF>(args.nl2, co);
       reverse_points(yb, dphi2);
     }
