@@ -11,7 +11,7 @@
 // along one axis, conj-propagator transforms along y, conj-propagator
 // transforms along the other axis + reverse first half-step); the axes
 // alternate, so that the end of one step and the beginning of the next are
-// one pass.  dJ/dPhi at the
+// one pass (three fields on large grids: x first, tau last, step by step).  dJ/dPhi at the
 // six stage positions of every step is reduced on the device in a fixed
 // order and turned into dJ/ddk_n on the host: with Phi(z) = Phi_n +
 // dk_n (z - z_n) and Phi_n = dz sum_{m<n} dk_m,
@@ -55,6 +55,13 @@ int pass_blocks(int axis, const brahms_plan_s& p) {
   const int n = axis == AX_X ? p.nx : p.nt;
   const long lines = axis == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
   return brahms::detail::adjoint_blocks(axis, lines, n);
+}
+
+// Those of a pass with the fields together (no more: its blocks are longer).
+int together_blocks(int axis, const brahms_plan_s& p) {
+  const long lines = axis == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
+  const int lpb = lines_per_block(axis == AX_X ? p.nx : p.nt);
+  return int((lines + lpb - 1) / lpb);
 }
 
 AdjLayout adj_layout(const brahms_plan_s& p, int nsteps, int every) {
@@ -110,13 +117,13 @@ brahms_status copy_state(const brahms_plan_s& p, float2* const* dst, float2* con
 
 // One adjoint pass along ax with the reverse RK4 of step `row`'s second
 // half-step (at = VJP_FIRST), of its first one (VJP_LAST), or of its first one
-// and step row - 1's second one (VJP_PAIR).  Their inputs are the segment's
+// and step row - 1's second one (VJP_PAIR); with or without VJP_TOGETHER.  Their inputs are the segment's
 // saved ones; their per-block phase derivatives go to slots (row, 1), (row, 0)
 // and (row - 1, 1) of its partials.
 brahms_status adj_pass(brahms_plan_s& p, const AdjLayout& L, int set, int row, int ax, int at,
                        float2* const* g) {
   const int per_field = p.nx + p.ny + p.nt;
-  const int trow = set * kSetRows + row, half = at == VJP_FIRST ? 1 : 0;
+  const int trow = set * kSetRows + row, half = (at & ~VJP_TOGETHER) == VJP_FIRST ? 1 : 0;
   double* parts = reinterpret_cast<double*>(p.adj_ws + L.parts[set]);
   auto slot = [&](int r, int h) { return parts + (size_t(r) * 2 + h) * size_t(L.max_blocks) * 3; };
   AdjArgs a{};
@@ -191,6 +198,25 @@ brahms_status reverse_segment(brahms_plan_s& p, const AdjLayout& L, int c, int s
                               double* dphi) {
   const long long s0 = p.adj_n0 + (long long)c * p.adj_every;
   const int cnt = int(std::min<long long>(p.adj_every, p.adj_n0 + p.adj_nsteps - s0));
+  const double* parts = reinterpret_cast<const double*>(p.adj_ws + L.parts[set]);
+  // Step by step, x first and tau last, where a pass is better with the fields
+  // together: both of them, or one in a segment of one step, which has no pairs.
+  const bool tx = brahms::detail::adjoint_together(p, AX_X), tt = brahms::detail::adjoint_together(p, AX_T);
+  if ((tx && tt) || ((tx || tt) && cnt == 1)) {
+    const int first = VJP_FIRST | (tx ? VJP_TOGETHER : 0), last = VJP_LAST | (tt ? VJP_TOGETHER : 0);
+    for (int i = cnt - 1; i >= 0; --i) {
+      if (brahms_status st = adj_pass(p, L, set, i, AX_X, first, g)) return st;
+      if (brahms_status st = brahms::detail::launch_linear_pass(p, set * kSetRows + i, AX_Y, g, true))
+        return st;
+      if (brahms_status st = adj_pass(p, L, set, i, AX_T, last, g)) return st;
+    }
+    const int nb_x = tx ? together_blocks(AX_X, p) : pass_blocks(AX_X, p);
+    const int nb_t = tt ? together_blocks(AX_T, p) : pass_blocks(AX_T, p);
+    hipLaunchKernelGGL(reduce_dphi_segment, dim3(unsigned(cnt), 2), dim3(256), 0, p.stream, parts, nb_t, nb_x,
+                       nb_t, nb_x, L.max_blocks, dphi + 6 * (s0 - p.adj_n0));
+    HIP_TRY(hipGetLastError());
+    return BRAHMS_OK;
+  }
   // The sweep takes the axes of every other step the other way round (they
   // commute), so that the last axis of one step is the first of the next one
   // it comes to, and one pass does both.
@@ -204,9 +230,8 @@ brahms_status reverse_segment(brahms_plan_s& p, const AdjLayout& L, int c, int s
   }
   // dJ/dPhi of the segment's steps, in a fixed order
   const int nb_first = pass_blocks(ends[1], p), nb_last = pass_blocks(ends[0], p);
-  hipLaunchKernelGGL(reduce_dphi_segment, dim3(unsigned(cnt), 2), dim3(256), 0, p.stream,
-                     reinterpret_cast<const double*>(p.adj_ws + L.parts[set]), nb_first, nb_last,
-                     L.max_blocks, dphi + 6 * (s0 - p.adj_n0));
+  hipLaunchKernelGGL(reduce_dphi_segment, dim3(unsigned(cnt), 2), dim3(256), 0, p.stream, parts, nb_first, nb_last,
+                     nb_last, nb_first, L.max_blocks, dphi + 6 * (s0 - p.adj_n0));
   HIP_TRY(hipGetLastError());
   return BRAHMS_OK;
 }

@@ -122,6 +122,9 @@ __device__ inline void rk4_vjp_point(const float2* y, float2* g, const float2 (*
 // reduction in double) go to dphi_out[block], three for each reverse RK4.
 // ---------------------------------------------------------------------------
 enum VjpWhere { VJP_FIRST = 1, VJP_LAST = 2, VJP_PAIR = 3 };
+// Added to VJP_FIRST (x) or VJP_LAST (tau) for the launcher: the three fields
+// together in a thread (adjoint_pass_together).
+constexpr int VJP_TOGETHER = 4;
 
 struct AdjArgs {
   float2* g[3];             // cotangent fields, in place
@@ -164,18 +167,17 @@ __device__ __forceinline__ void reduce_dphi(const double* dphi, double (*s_red)[
   }
 }
 
-// One field per thread at every size (see axis_pass_split_body), the saved
-// half-step inputs of a thread's points loaded with its cotangents; the
-// reverse RK4 goes point by point (the asm ties: all points at once take 256
-// registers and leave one wave per SIMD).  A fields-together pass holds four
-// values per point of both fields and more; with the saved states in memory
-// (not in a cache) 128 x 128 x 64 and two fields: x last 26.4 against 18.4
-// us, x first 23.5 / 18.5, tau first 18.3 / 17.8; 128^3, x first 33.1 / 33.0,
-// tau first 33.6 / 32.2 (three fields, tau first 46.9 / 66.3, the one form
-// that lost, but x last 65.7 / 44.6).  What bounds it: six field transfers,
-// 50 MB at 128 x 128 x 64, 10 us; the rest is the chain of two waves a SIMD.
-// A pair moves eight where two passes move twelve: 29-30 us against 19 + 20
-// (beside the next segment's forward steps on the other stream).
+// One field per thread (see axis_pass_split_body), the saved half-step inputs
+// of a thread's points loaded with its cotangents; the reverse RK4 goes point
+// by point (the asm ties: all points at once take 256 registers and leave one
+// wave per SIMD).  Two fields at every size: with the saved states in memory
+// (not in a cache) 128 x 128 x 64: x last 18.4 us (fields together: 26.4), x
+// first 18.5 / 23.5, tau first 17.8 / 18.3; 128^3, x first 33.0 / 33.1, tau
+// first 32.2 / 33.6.  What bounds it: six field transfers, 50 MB at 128 x 128 x
+// 64, 10 us; the rest is the chain of two waves a SIMD.  A pair moves eight
+// where two passes move twelve: 29-30 us against 19 + 20 (beside the next
+// segment's forward steps on the other stream).  Three fields: where
+// adjoint_together (launch.hpp) does not prefer the other form.
 template <int N1, int N2, int AX, int NF, int AT>
 __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(AdjArgs args) {
   constexpr int T = split_threads(N2, AX), BLOCK = NF * T;
@@ -311,17 +313,103 @@ __global__ __launch_bounds__((NF * split_threads(N2, AX))) void adjoint_pass(Adj
   }
 }
 
+// Three fields, together in a thread: the reverse RK4 point by point on the
+// thread's own values (no exchange between threads), the saved states read
+// where they are used.  Only what adjoint_together takes: FIRST on x and LAST
+// on tau (a step's axes commute, and these are the faster two), step by step
+// rather than in pairs.  167-216 registers, two or three waves per SIMD; 18
+// field transfers a step (with y) at 3.5 TB/s.  128^3, 20 steps: 4622 -> 4361
+// us against pairs of one field per thread (recording beside), 256 x 128 x 128,
+// 16 steps: 6050 -> 5566.
+template <int N1, int N2, int AX, int AT>
+__global__ __launch_bounds__(kBlock) void adjoint_pass_together(AdjArgs args) {
+  constexpr int NF = 3;
+  using G = LineGeom<N1, N2>;
+  constexpr int N = G::N;
+  constexpr bool WL = AX == AX_X && N2 <= 64 && 64 % N2 == 0;
+  static_assert((AX == AX_X && AT == VJP_FIRST) || (AX == AX_T && AT == VJP_LAST), "x first, tau last");
+  __shared__ float2 lds[G::LDS_ELEMS];
+  __shared__ float2 s_tw[N], s_prop[NF * N];
+  __shared__ double s_red[3][kBlock];
+
+  const int tid = threadIdx.x;
+  const int t = AX == AX_X ? tid % N2 : tid / G::LPB;
+  const int li = AX == AX_X ? tid / N2 : tid % G::LPB;
+  const unsigned bx = AX == AX_X ? slab_tile(args, blockIdx.x) : blockIdx.x;
+  const LineAddr la = line_addr<AX, N>(args, bx * unsigned(G::LPB) + unsigned(li));
+  const unsigned idx0 = la.base + unsigned(t) * la.estride;
+  const unsigned field_bytes = unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) * 8u;
+  const unsigned lane_bytes = idx0 * 8u, slot_bytes = unsigned(N2) * la.estride * 8u;
+  float2* lbuf = (N2 > 1) ? lds + li * G::LSTRIDE : lds;
+  const DftConsts K = *args.consts;
+  float2 co[NF][kNlCoef];
+  load_coefficients<NF>(args.nl, co);
+  float sigma[NF];
+  __amdgpu_buffer_rsrc_t rg[NF], ry[NF];
+#pragma unroll
+  for (int j = 0; j < NF; ++j) {
+    sigma[j] = args.sigma[j];
+    rg[j] = field_rsrc(args.g[j], field_bytes);
+    ry[j] = field_rsrc(args.y[j], field_bytes);
+  }
+  StageTables<N, NF, kBlock, false> st;
+  st.begin(args, 0, tid);
+  float2 v[NF][N1];
+#pragma unroll
+  for (int j = 0; j < NF; ++j)
+#pragma unroll
+    for (int e = 0; e < N1; ++e) v[j][e] = load_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes);
+  st.end(false, tid, s_tw, s_prop, s_tw, s_prop);
+  __syncthreads();  // s_tw, s_prop staged
+  LaneTwiddles<N1, N2, false> tw;
+  tw.init(s_tw, t);
+
+  double dphi[3] = {0.0, 0.0, 0.0};
+  auto reverse_rk4 = [&]() {
+#pragma unroll
+    for (int e = 0; e < N1; ++e) {
+      float2 yy[NF], gg[NF];
+#pragma unroll
+      for (int j = 0; j < NF; ++j) {
+        yy[j] = load_slot<false>(ry[j], lane_bytes, unsigned(e) * slot_bytes);
+        gg[j] = v[j][e];
+      }
+      // one point at a time (an empty asm, no instructions)
+#pragma unroll
+      for (int j = 0; j < NF; ++j)
+        asm volatile("" : "+v"(yy[j].x), "+v"(yy[j].y), "+v"(gg[j].x), "+v"(gg[j].y), "+v"(dphi[0]),
+                          "+v"(dphi[1]), "+v"(dphi[2]));
+      rk4_vjp_point<NF>(yy, gg, co, sigma, dphi);
+#pragma unroll
+      for (int j = 0; j < NF; ++j) v[j][e] = gg[j];
+    }
+  };
+  if constexpr (AT == VJP_FIRST) reverse_rk4();
+  line_trip<N1, N2, NF, WL, true>(v, tw, t, lbuf, s_prop, K);
+  if (la.valid) {   // (the RK4 inside: it would be moved down to the stores, away from its states)
+    if constexpr (AT == VJP_LAST) reverse_rk4();
+#pragma unroll
+    for (int j = 0; j < NF; ++j)
+#pragma unroll
+      for (int e = 0; e < N1; ++e) store_slot<false>(rg[j], lane_bytes, unsigned(e) * slot_bytes, v[j][e]);
+  } else {   // a line past the last one counts for nothing
+    dphi[0] = dphi[1] = dphi[2] = 0.0;
+  }
+  reduce_dphi<kBlock, kBlock>(dphi, s_red, args.dphi_out);
+}
+
 // Sum the per-block phase derivatives of a segment's adjoint passes (fixed
 // order).  Block (i, w) handles step i of the segment and pass w (0: the
 // reverse first half-step, 1: the reverse second half-step), which wrote
 // parts[((i * 2 + w) * stride + b) * 3 + k] for its blocks b; out[6 i + 3 w +
-// k] receives the sum over b (block size 256).  The sweep's axes alternate:
-// nblocks[w] blocks in the segment's last step and every second one before.
-static __global__ void reduce_dphi_segment(const double* parts, int nblocks0, int nblocks1,
+// k] receives the sum over b (block size 256).  The axes may alternate: pass w
+// has last_w blocks in the segment's last step and every second one before,
+// other_w in those between.
+static __global__ void reduce_dphi_segment(const double* parts, int last_0, int last_1, int other_0, int other_1,
                                            int stride, double* out) {
   __shared__ double s[256];
   const int i = blockIdx.x, w = blockIdx.y;
-  const int nb = ((int(gridDim.x) - 1 - i + w) & 1) == 0 ? nblocks0 : nblocks1;
+  const int nb = ((int(gridDim.x) - 1 - i) & 1) == 0 ? (w == 0 ? last_0 : last_1) : (w == 0 ? other_0 : other_1);
   const double* src = parts + (size_t(i) * 2 + w) * size_t(stride) * 3;
   for (int k = 0; k < 3; ++k) {
     double acc = 0.0;

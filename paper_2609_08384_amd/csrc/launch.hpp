@@ -56,8 +56,22 @@ inline int adjoint_blocks(int axis, long lines, int n) {
   return int((lines + lpb - 1) / lpb);
 }
 
+// Whether a reverse pass of a plan along x or tau is better with the fields
+// together in a thread (adjoint_pass_together) than with one field per thread:
+// three fields, a launch that fills the chip, and room for three fields in a
+// lane.  128^3: x, reverse half-step first, 45 against 56 us; tau, last, 42 /
+// 64.  Not with 24 values of a field in a lane, where three of them leave one
+// wave per SIMD (192 x 128 x 96, 16 steps: 4580 / 3694 us), nor in launches of
+// few waves (narrow_launch; 128 x 128 x 64: 1990 / 1837).
+inline bool adjoint_together(const brahms_plan_s& p, int axis) {
+  const int n = axis == AX_X ? p.nx : p.nt, n2 = kBlock / lines_per_block(n);
+  const long long lines = axis == AX_X ? (long long)p.ny * p.nt : (long long)p.nx * p.ny;
+  return p.nf == 3 && n / n2 <= 16 && !narrow_launch(lines, n2);
+}
+
 // One adjoint pass (conj-propagator transforms with the RK4 half-step's VJP)
-// along x or tau (VJP_* of adjoint.hpp).
+// along x or tau (VJP_* of adjoint.hpp; with VJP_TOGETHER where
+// adjoint_together says so).
 template <int N1, int N2>
 void launch_adj_axis(int axis, int at, const brahms_plan_s& p, const AdjArgs& a);
 

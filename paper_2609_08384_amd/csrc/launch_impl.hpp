@@ -258,17 +258,29 @@ void launch_group_long(int nl, const GroupGeom& g, hipStream_t st, const PassArg
 // ---------------------------------------------------------------------------
 // adjoint passes (x or tau, with the VJP of the half-step they undo)
 // ---------------------------------------------------------------------------
+// (the block counts are pass_blocks' and together_blocks' in adjoint.hip)
+template <int AX>
+long adjoint_lines(const brahms_plan_s& p) {
+  return AX == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
+}
+
 template <int N1, int N2, int AX, int NF, int AT>
 void launch_adj(const brahms_plan_s& p, const AdjArgs& a) {
-  const long lines = AX == AX_X ? long(p.ny) * p.nt : long(p.nx) * p.ny;
   constexpr int T = split_threads(N2, AX);
-  // (the block counts are adjoint_blocks' in launch.hpp)
-  hipLaunchKernelGGL((adjoint_pass<N1, N2, AX, NF, AT>), dim3(blocks_of(lines, T / N2)), dim3(NF * T), 0, p.stream,
-                     a);
+  hipLaunchKernelGGL((adjoint_pass<N1, N2, AX, NF, AT>), dim3(blocks_of(adjoint_lines<AX>(p), T / N2)), dim3(NF * T),
+                     0, p.stream, a);
 }
 
 template <int N1, int N2, int AX, int NF>
 void launch_adj_at(int at, const brahms_plan_s& p, const AdjArgs& a) {
+  if constexpr (NF == 3 && N1 <= 16) {
+    constexpr int AT = AX == AX_X ? VJP_FIRST : VJP_LAST;
+    if (at == (AT | VJP_TOGETHER)) {
+      hipLaunchKernelGGL((adjoint_pass_together<N1, N2, AX, AT>),
+                         dim3(blocks_of(adjoint_lines<AX>(p), LineGeom<N1, N2>::LPB)), dim3(kBlock), 0, p.stream, a);
+      return;
+    }
+  }
   if (at == VJP_PAIR) launch_adj<N1, N2, AX, NF, VJP_PAIR>(p, a);
   else if (at == VJP_FIRST) launch_adj<N1, N2, AX, NF, VJP_FIRST>(p, a);
   else launch_adj<N1, N2, AX, NF, VJP_LAST>(p, a);

@@ -72,7 +72,7 @@ SCRATCH = 32
 
 
 @pytest.mark.parametrize("family", ["axis_pass", "axis_pass_batched", "axis_pass_split", "axis_pass_split_batched",
-                                    "line_steps", "line_steps_batched", "adjoint_pass"])
+                                    "line_steps", "line_steps_batched", "adjoint_pass", "adjoint_pass_together"])
 def test_passes_keep_their_values_in_registers(kernels, family):
     mine = {args: k[".private_segment_fixed_size"] for (name, args), k in kernels.items() if name == family}
     assert mine
