@@ -184,11 +184,15 @@ brahms_status brahms_plan_destroy(brahms_plan plan);
  *   adjoint runs with orders 0 and 1 only; a tau axis longer than 256 always
  *   takes x, y and its three tau passes)
  *   graph 1: brahms_step replays whole 64-step chunks (tables and passes) from
- *     a hipGraph captured once per binding and schedule (bitwise the same
- *     result; removes the per-launch host cost).  Chunks that record timing,
+ *     a hipGraph captured once per binding and schedule, or, with literal
+ *     half-steps in pairs, from one of two: for chunks that begin with an
+ *     even step and with an odd one (bitwise the same result; removes the
+ *     per-launch host cost).  Chunks that record timing,
  *     monitors or snapshots, partial chunks, and plans whose transverse map
- *     tables are filled per step run launch by launch.  The graph is captured
- *     by brahms_plan_set_schedule or brahms_plan_bind, whichever comes last.
+ *     tables hold less than a chunk run launch by launch.  The graph is captured
+ *     by brahms_plan_set_schedule or brahms_plan_bind, whichever comes last
+ *     (of two, the one for the plan's step index then; the other by the first
+ *     call that replays it).
  *   merge_halves 1: within one brahms_step call, the second RK4 half-step of
  *     step n and the first of step n + 1 (Eq. expon: N/2 - L - N/2 repeated)
  *     run as one classical RK4 step of size dz from z_n + dz/2.  The exact

@@ -510,20 +510,30 @@ bool graph_chunk_ok(const brahms_plan_s& p) {
          (p.dk_map.empty() || p.map_rows == kChunk);
 }
 
-void drop_chunk_graph(brahms_plan_s& p) {
-  if (p.chunk_exec) (void)hipGraphExecDestroy(p.chunk_exec);
-  if (p.chunk_graph) (void)hipGraphDestroy(p.chunk_graph);
-  p.chunk_exec = nullptr;
-  p.chunk_graph = nullptr;
+// Which of the plan's two graphs replays a chunk from step n: steps in pairs
+// run odd step indices with the axes the other way round.
+int chunk_parity(const brahms_plan_s& p, long long n) { return detail::pairing(p) ? int(n & 1) : 0; }
+
+void drop_chunk_graph(brahms_plan_s& p, int parity) {
+  if (p.chunk_exec[parity]) (void)hipGraphExecDestroy(p.chunk_exec[parity]);
+  if (p.chunk_graph[parity]) (void)hipGraphDestroy(p.chunk_graph[parity]);
+  p.chunk_exec[parity] = nullptr;
+  p.chunk_graph[parity] = nullptr;
+}
+
+void drop_chunk_graphs(brahms_plan_s& p) {
+  drop_chunk_graph(p, 0);
+  drop_chunk_graph(p, 1);
 }
 
 // Capture the tables and the 64 steps of one chunk on a private stream; the
 // tables read the chunk's first step (and, with merged halves, the run's last
 // step) from the workspace, set before each replay; everything else is the
 // same for every chunk.  With merged halves the captured chunk continues a
-// run: none of its steps has a first half-step of its own.
-brahms_status build_chunk_graph(brahms_plan_s& p) {
-  drop_chunk_graph(p);
+// run: none of its steps has a first half-step of its own.  With steps in
+// pairs the chunk begins with a step of the given parity (chunk_parity).
+brahms_status build_chunk_graph(brahms_plan_s& p, int parity) {
+  drop_chunk_graph(p, parity);
   if (!p.capture_stream) HIP_TRY(hipStreamCreateWithFlags(&p.capture_stream, hipStreamNonBlocking));
   const hipStream_t user = p.stream;
   const long long saved_n0 = p.table_n0;
@@ -545,16 +555,16 @@ brahms_status build_chunk_graph(brahms_plan_s& p) {
       st = detail::refresh_tables(p, 0, kChunk);
       if (line && st == BRAHMS_OK) st = detail::launch_line(p, 0, kChunk, continued);
       for (int s = 0; s < kChunk && st == BRAHMS_OK && !line; ++s)
-        st = pairs ? detail::launch_fused_step(p, s, s == 0, s == kChunk - 1, (s & 1) != 0)   // (from an even step)
+        st = pairs ? detail::launch_fused_step(p, s, s == 0, s == kChunk - 1, ((s + parity) & 1) != 0)
                    : detail::launch_step(p, s, io, continued, false);
     }
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(p.capture_stream, &g);
     if (st == BRAHMS_OK && e == hipSuccess) {
-      p.chunk_graph = g;
+      p.chunk_graph[parity] = g;
       hipGraphExec_t exec = nullptr;
       e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
-      if (e == hipSuccess) p.chunk_exec = exec;   // drop_chunk_graph releases only what exists
+      if (e == hipSuccess) p.chunk_exec[parity] = exec;   // drop_chunk_graph releases only what exists
     } else if (g) {
       (void)hipGraphDestroy(g);
     }
@@ -563,11 +573,11 @@ brahms_status build_chunk_graph(brahms_plan_s& p) {
   p.table_n0_dev = nullptr;
   p.table_n0 = saved_n0;
   if (st != BRAHMS_OK) {
-    drop_chunk_graph(p);
+    drop_chunk_graph(p, parity);
     return st;
   }
   if (e != hipSuccess) {
-    drop_chunk_graph(p);
+    drop_chunk_graph(p, parity);
     return fail(BRAHMS_E_DEVICE, std::string("chunk graph capture: ") + hipGetErrorString(e));
   }
   return BRAHMS_OK;
@@ -590,12 +600,12 @@ brahms_status run_fused(brahms_plan_s& p, int nsteps) {
   while (done < nsteps) {
     const int count = std::min(kChunk, nsteps - done);
     if (count == kChunk && graph_chunk_ok(p) && done > 0 && done + kChunk < nsteps) {
-      if (!p.chunk_exec)
-        if (brahms_status st = build_chunk_graph(p)) return st;
+      if (!p.chunk_exec[0])
+        if (brahms_status st = build_chunk_graph(p, 0)) return st;
       hipLaunchKernelGGL(set_step_index, dim3(1), dim3(1), 0, p.stream,
                          reinterpret_cast<long long*>(p.ws + p.off_n0), p.step, merge_last);
       HIP_TRY(hipGetLastError());
-      HIP_TRY(hipGraphLaunch(p.chunk_exec, p.stream));
+      HIP_TRY(hipGraphLaunch(p.chunk_exec[0], p.stream));
       p.table_n0 = p.step;
       p.step += count;
       done += count;
@@ -624,20 +634,21 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
   const bool row_maps = p.dk_map.empty() || p.map_rows == kChunk;
   const bool line = !detail::long_tau(p) && detail::step_passes(p).n == 1;
   const long long merge_last = merge ? p.step + nsteps - 1 : -1;
+  // (a chunk has as many steps as the map's tables hold)
+  const int chunk = p.dk_map.empty() || p.map_rows == 1 ? kChunk : p.map_rows;
   int done = 0;
   while (done < nsteps) {
-    int count = std::min(kChunk, nsteps - done);
-    // a captured chunk of pairs begins with an even step
-    if (pairs && graph_chunk_ok(p) && (p.step & 1) != 0) count = 1;
+    const int count = std::min(chunk, nsteps - done);
     // a captured chunk has no leading half-step when merging, so the call's
     // first chunk runs eagerly
     if (count == kChunk && graph_chunk_ok(p) && !(merge && done == 0)) {
-      if (!p.chunk_exec)
-        if (brahms_status st = build_chunk_graph(p)) return st;
+      const int parity = chunk_parity(p, p.step);
+      if (!p.chunk_exec[parity])
+        if (brahms_status st = build_chunk_graph(p, parity)) return st;
       hipLaunchKernelGGL(set_step_index, dim3(1), dim3(1), 0, p.stream,
                          reinterpret_cast<long long*>(p.ws + p.off_n0), p.step, merge_last);
       HIP_TRY(hipGetLastError());
-      HIP_TRY(hipGraphLaunch(p.chunk_exec, p.stream));
+      HIP_TRY(hipGraphLaunch(p.chunk_exec[parity], p.stream));
       p.table_n0 = p.step;
       p.step += count;
       done += count;
@@ -765,7 +776,7 @@ brahms_status brahms_plan_bind(brahms_plan plan, void* const* fields, void* work
   }
   plan->bound = false;
   plan->adj_ready = false;
-  drop_chunk_graph(*plan);   // it holds the old pointers
+  drop_chunk_graphs(*plan);   // they hold the old pointers
   for (int j = 0; j < 3; ++j) plan->fields[j] = j < plan->nf ? static_cast<float2*>(fields[j]) : nullptr;
   plan->ws = static_cast<char*>(workspace);
   if (!plan->dk.empty()) {
@@ -788,7 +799,7 @@ brahms_status brahms_plan_bind(brahms_plan plan, void* const* fields, void* work
     HIP_TRY(hipStreamSynchronize(plan->stream));
   }
   plan->bound = true;
-  if (graph_chunk_ok(*plan)) return build_chunk_graph(*plan);
+  if (graph_chunk_ok(*plan)) return build_chunk_graph(*plan, chunk_parity(*plan, plan->step));
   return BRAHMS_OK;
 }
 
@@ -877,7 +888,7 @@ brahms_status brahms_plan_set_schedule(brahms_plan plan, const brahms_schedule* 
   if (plan->order != sched->pass_order || plan->use_graph != (sched->graph != 0) ||
       plan->merge != (sched->merge_halves != 0) || plan->fuse != (sched->fuse_steps != 0) ||
       plan->split != sched->split || plan->wide != sched->wide)
-    drop_chunk_graph(*plan);
+    drop_chunk_graphs(*plan);
   plan->order = sched->pass_order;
   plan->split = sched->split;
   plan->wide = sched->wide;
@@ -885,7 +896,8 @@ brahms_status brahms_plan_set_schedule(brahms_plan plan, const brahms_schedule* 
   plan->merge = sched->merge_halves != 0;
   plan->fuse = sched->fuse_steps != 0;
   // capture now rather than in the first call that replays it
-  if (graph_chunk_ok(*plan) && !plan->chunk_exec) return build_chunk_graph(*plan);
+  const int parity = chunk_parity(*plan, plan->step);
+  if (graph_chunk_ok(*plan) && !plan->chunk_exec[parity]) return build_chunk_graph(*plan, parity);
   return BRAHMS_OK;
 }
 
@@ -937,7 +949,7 @@ brahms_status brahms_plan_destroy(brahms_plan plan) {
     (void)hipEventDestroy(t.stop);
   }
   for (hipEvent_t e : plan->pool) (void)hipEventDestroy(e);
-  drop_chunk_graph(*plan);
+  drop_chunk_graphs(*plan);
   if (plan->capture_stream) (void)hipStreamDestroy(plan->capture_stream);
   for (hipEvent_t e : plan->adj_ev)
     if (e) (void)hipEventDestroy(e);

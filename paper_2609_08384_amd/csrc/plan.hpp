@@ -41,8 +41,8 @@ struct brahms_plan_s {
   int wide = 0;
   // hipGraph replay of whole 64-step chunks (schedule field `graph`)
   bool use_graph = false;
-  hipGraph_t chunk_graph = nullptr;
-  hipGraphExec_t chunk_exec = nullptr;
+  hipGraph_t chunk_graph[2] = {};         // of chunks from an even and from an odd step
+  hipGraphExec_t chunk_exec[2] = {};      // (steps in pairs; others use the first)
   hipStream_t capture_stream = nullptr;   // private stream the chunk is captured on
   const long long* table_n0_dev = nullptr;  // while capturing: tables read n0
                                             // and merge_last here

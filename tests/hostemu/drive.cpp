@@ -600,6 +600,26 @@ void scenario_maps() {
   std::printf("maps: ok\n");
 }
 
+// chunks replayed from a graph, from even and odd steps: plane waves, two axes
+// and three, literal and merged; every whole chunk is a replay
+void scenario_graph_chunks() {
+  Rng r(107);
+  const int spec[3][4] = {{1, 1, 64, 2}, {16, 12, 1, 2}, {8, 6, 12, 3}};
+  for (auto& s : spec)
+    for (int merge : {0, 1}) {
+      Problem p = make_problem(r, s[0], s[1], s[2], s[3], 300, false, 0.7);
+      const std::vector<int> calls = {3, 64, 130, 1, 64};
+      const auto eager = run_calls(p, schedule(0, 0, merge), calls);
+      const long long before = emu::g_graph_launches;
+      expect_equal(eager, run_calls(p, schedule(0, 1, merge), calls), "graph replay from odd steps");
+      // (merged: a call's first chunk is launched step by step)
+      const long long want = merge ? 1 : 4;
+      if (emu::g_graph_launches - before != want)
+        emu::die("graph launches " + std::to_string(emu::g_graph_launches - before) + ", not " + std::to_string(want));
+    }
+  std::printf("graph chunks: ok\n");
+}
+
 // the adjoint: segments of one step and of several, the last one shorter, a
 // second stream's segment beside the sweep
 void scenario_adjoint() {
@@ -650,6 +670,7 @@ int main(int argc, char** argv) {
   else if (s == "stream_graphs") scenario_stream_graphs();
   else if (s == "splits") scenario_splits();
   else if (s == "maps") scenario_maps();
+  else if (s == "graph_chunks") scenario_graph_chunks();
   else if (s == "adjoint") scenario_adjoint();
   else {
     std::fprintf(stderr, "unknown scenario %s\n", s.c_str());
