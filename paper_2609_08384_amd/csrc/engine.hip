@@ -131,18 +131,22 @@ void layout(brahms_plan_s& p) {
   p.off_n0 = off;
   off = align_up(off + 2 * sizeof(long long));
   if (!p.dk_map.empty()) {
-    // phase tables of a whole 64-step chunk when they take at most 64 MB,
-    // else one step at a time
-    const size_t row = sizeof(float2) * 5 * p.dk_map.size();
-    p.map_rows = row * kChunk <= (size_t(64) << 20) ? kChunk : 1;
     p.off_map = off;
     off = align_up(off + sizeof(double) * p.dk_map.size());
-    p.off_maptab = off;
-    off = align_up(off + row * size_t(p.map_rows));
     p.off_psi0 = off;
     off = align_up(off + sizeof(double) * (p.map_scale.size() + 1));
     p.off_scale = off;
     off = align_up(off + sizeof(double) * (p.map_scale.size() + 1));
+    // phase tables of a whole 64-step chunk when they take at most 64 MB, else
+    // of as many steps as keep the workspace within the no-allocation entry
+    // point's array (256 x 256: 11; steps run in pairs inside such a chunk); a
+    // long tau axis, whose steps have no pairs, one step at a time
+    p.off_maptab = off;
+    const size_t row = sizeof(float2) * 5 * p.dk_map.size();
+    if (row * kChunk <= (size_t(64) << 20)) p.map_rows = kChunk;
+    else if (brahms::detail::long_tau(p) || off + row > BRAHMS_NOALLOC_SCRATCH_BYTES) p.map_rows = 1;
+    else p.map_rows = int(std::min<size_t>(kChunk, (BRAHMS_NOALLOC_SCRATCH_BYTES - off) / row));
+    off = align_up(off + row * size_t(p.map_rows));
   }
   p.ws_size = off;
 }
@@ -260,7 +264,7 @@ bool fusing(const brahms_plan_s& p) {
 brahms_status refresh_tables(brahms_plan_s& p, long long n0, int count, int row0,
                              long long merge_last) {
   if (count < 0 || row0 < 0 || row0 + count > kTableRows ||
-      (!p.dk_map.empty() && p.map_rows == kChunk && count > kChunk))
+      (!p.dk_map.empty() && p.map_rows > 1 && count > p.map_rows))
     return fail(BRAHMS_E_INVALID_ARG, "table rows out of range");
   const int per_field = p.nx + p.ny + p.nt;
   TableArgs ta{};
@@ -285,7 +289,7 @@ brahms_status refresh_tables(brahms_plan_s& p, long long n0, int count, int row0
   if (brahms_status st = timing_start(p, 3)) return st;
   hipLaunchKernelGGL(step_tables, dim3(unsigned((total + 255) / 256)), dim3(256), 0, p.stream, ta);
   HIP_TRY(hipGetLastError());
-  if (!p.dk_map.empty() && p.map_rows == kChunk) {
+  if (!p.dk_map.empty() && p.map_rows > 1) {
     if (row0 != 0) return fail(BRAHMS_E_UNSUPPORTED, "map tables are filled from row 0");
     if (brahms_status st = map_table(p, n0, count)) return st;
   }
@@ -345,6 +349,8 @@ brahms_status map_table(brahms_plan_s& p, long long n0, int count) {
 
 bool pairing(const brahms_plan_s& p) {
   if (long_tau(p) || merging(p)) return false;
+  // (map tables of one step at a time: no pass has two steps' factors)
+  if (!p.dk_map.empty() && p.map_rows == 1) return false;
   return step_passes(p).n > 1;
 }
 
@@ -395,15 +401,11 @@ brahms_status launch_fused_step(brahms_plan_s& p, int row, bool first, bool last
   const int lead = odd ? b0 : a0, tail = odd ? a0 : b0;
   const bool literal = !merging(p);
   const bool map = !p.dk_map.empty();
-  if (map && p.map_rows == 1) {
-    if (!first || !last) return fail(BRAHMS_E_UNSUPPORTED, "step pairs with one-step map tables");
-    if (brahms_status st = map_table(p, p.table_n0 + row, 1)) return st;
-  }
   const int map_mode = map ? NL_MAP : 0;
   auto map_factors = [&](int r, int stage) -> const float2* {   // of a row's stage offset
     if (!map) return nullptr;
     return reinterpret_cast<const float2*>(p.ws + p.off_maptab) +
-           (size_t(p.map_rows == 1 ? 0 : r) * 5 + size_t(stage)) * p.dk_map.size();
+           (size_t(r) * 5 + size_t(stage)) * p.dk_map.size();
   };
   auto in_place = [&](PassArgs& a) {
     for (int j = 0; j < 3; ++j) {
@@ -631,7 +633,6 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
   // pairs up to the end of a chunk of tables or a step that a monitor or
   // snapshot looks at (the same bits wherever a run ends)
   const bool pairs = detail::pairing(p);
-  const bool row_maps = p.dk_map.empty() || p.map_rows == kChunk;
   const bool line = !detail::long_tau(p) && detail::step_passes(p).n == 1;
   const long long merge_last = merge ? p.step + nsteps - 1 : -1;
   // (a chunk has as many steps as the map's tables hold)
@@ -671,7 +672,7 @@ brahms_status run_steps(brahms_plan_s& p, int nsteps) {
     for (int s = 0; s < count && !line; ++s) {
       const long long n = p.step + s;
       if (pairs) {
-        const bool last = s == count - 1 || !row_maps || (watch && detail::step_watched(p, n + 1));
+        const bool last = s == count - 1 || (watch && detail::step_watched(p, n + 1));
         if (brahms_status st = detail::launch_fused_step(p, s, !open, last, (n & 1) != 0)) return st;
         open = !last;
       } else {

@@ -50,7 +50,7 @@ struct brahms_plan_s {
   size_t off_phi0 = 0, off_dk = 0, off_prop = 0, off_nl = 0, off_flag = 0, ws_size = 0;
   size_t off_map = 0, off_maptab = 0;   // map (FP64) and its per-step phase tables
   size_t off_psi0 = 0, off_scale = 0;   // Psi_n prefix and s_n (with a scale profile)
-  int map_rows = 0;                     // steps per phase-table fill (kChunk or 1)
+  int map_rows = 0;                     // steps per phase-table fill
   size_t off_diag = 0;                  // partial sums of the diagnostics
   size_t off_n0 = 0;                    // first step of the chunk a graph replays
   // launch timing (diagnostics)
@@ -158,7 +158,9 @@ StepPasses step_passes(const brahms_plan_s& p);
 // Whether steps with literal half-steps alternate their axis order (odd step
 // indices run it backwards, whatever call they belong to), so that the end of
 // one step and the beginning of the next are along one axis and run as one
-// pass: steps of two or three passes.
+// pass: steps of two or three passes, and not with a transverse map whose
+// tables hold one step (alternating without pairs is not worth it: 256 x 256 x
+// 64 and pass order 1, 3 % longer with two fields, 7 % with three).
 bool pairing(const brahms_plan_s& p);
 // One z-step with the tables of `row`; with continued = true the step's first
 // half-step is left out (it was merged into the previous step's second one);

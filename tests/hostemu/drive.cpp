@@ -600,6 +600,32 @@ void scenario_maps() {
   std::printf("maps: ok\n");
 }
 
+// a map on a plane whose tables hold fewer steps than a chunk (27 here): steps
+// run in pairs up to the end of the tables; the workspace stays within the
+// no-allocation entry point's array
+void scenario_large_map() {
+  Rng r(103);
+  Problem p = make_problem(r, 192, 144, 2, 2, 3, false, 0.7);
+  std::vector<double> map(size_t(p.nx) * p.ny);
+  for (double& v : map) v = r.uniform(-2, 2);
+  p.prm.dk_map = map.data();
+  for (int order : {0, 1}) {
+    emu::g_axes.clear();
+    run_calls(p, schedule(order), {3});
+    const std::string want = order == 0 ? "xytyxyt" : "tyxytyx";
+    if (emu::g_axes != want) emu::die("large map: axes " + emu::g_axes + ", not " + want);
+    emu::g_axes.clear();
+    set_profile(p);
+    brahms_plan plan = nullptr;
+    OK(brahms_plan_create(p.nx, p.ny, p.nt, p.nf, &p.prm, nullptr, &plan));
+    size_t bytes = 0;
+    OK(brahms_plan_workspace_size(plan, &bytes));
+    OK(brahms_plan_destroy(plan));
+    if (bytes > BRAHMS_NOALLOC_SCRATCH_BYTES) emu::die("large map: workspace " + std::to_string(bytes));
+  }
+  std::printf("large map: ok\n");
+}
+
 // chunks replayed from a graph, from even and odd steps: plane waves, two axes
 // and three, literal and merged; every whole chunk is a replay
 void scenario_graph_chunks() {
@@ -670,6 +696,7 @@ int main(int argc, char** argv) {
   else if (s == "stream_graphs") scenario_stream_graphs();
   else if (s == "splits") scenario_splits();
   else if (s == "maps") scenario_maps();
+  else if (s == "large_map") scenario_large_map();
   else if (s == "graph_chunks") scenario_graph_chunks();
   else if (s == "adjoint") scenario_adjoint();
   else {
