@@ -147,6 +147,7 @@ brahms_status adj_pass(brahms_plan_s& p, const AdjLayout& L, int set, int row, i
     a.dphi_out2 = slot(row - 1, 1);
   }
   a.field_stride = per_field;
+  a.slab = brahms::detail::slab_tiles(p) ? 1 : 0;   // (orders 0 and 1)
   a.nx = p.nx; a.ny = p.ny; a.nt = p.nt;
   // exp(-i Phi) on the sum-frequency field, exp(+i Phi) on the others
   if (p.nf == 3) {

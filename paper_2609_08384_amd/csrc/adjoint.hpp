@@ -141,6 +141,7 @@ struct AdjArgs {
   const DftConsts* consts2;
   double* dphi_out2;
   int nx, ny, nt;
+  int slab;                 // as in PassArgs
   int axis_off, field_stride;
   float sigma[3];
 };

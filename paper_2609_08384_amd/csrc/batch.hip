@@ -342,6 +342,9 @@ brahms_status upload_descriptors(brahms_batch_s& b) {
           }
           a.tile_mul = 1;
           a.tiles = 1;
+          // (as xy_neighbours; a batch's long tau axes have no pairs)
+          const bool near = brahms::detail::long_tau(p) || p.order < 2 || (b.merge && !fused);
+          a.slab = near && brahms::detail::slab_tiles(p) ? 1 : 0;
           if (ax == AX_T) {
             const long lines = long(p.nx) * p.ny;
             const int lpb = lines_per_block(len, ((p.split >> ax) & 1) != 0);

@@ -263,6 +263,11 @@ bool fusing(const brahms_plan_s& p) {
   return n == 2 || (p.fuse && n >= 3);
 }
 
+bool xy_neighbours(const brahms_plan_s& p) {
+  if (long_tau(p)) return !fusing(p);
+  return p.order < 2 || !p.dk_map.empty() || (merging(p) && !fusing(p));
+}
+
 brahms_status refresh_tables(brahms_plan_s& p, long long n0, int count, int row0,
                              long long merge_last) {
   if (count < 0 || row0 < 0 || row0 + count > kTableRows ||
@@ -312,6 +317,7 @@ PassArgs pass_args(const brahms_plan_s& p, int row, int ax) {
   a.nx = p.nx; a.ny = p.ny; a.nt = p.nt;
   a.prop = r;
   a.field_stride = per_field;
+  a.slab = slab_tiles(p) && xy_neighbours(p) ? 1 : 0;
   return a;
 }
 

@@ -63,6 +63,7 @@ struct PassArgs {
   float2* pre[3];        // if pre[0]: the last pass also stores its values
                          // just before the RK4 half-step here
   int conj;              // multiply by conj(P) (adjoint linear step)
+  int slab;              // x and y passes: tiles in slabs (slab_tile)
   const float2* tw;      // this step's forward twiddles exp(-2 pi i m / N), m < N
   const float2* prop;    // this step's propagators, field j's table of this
                          // axis at prop + j * field_stride + axis_off
@@ -574,19 +575,17 @@ constexpr bool twiddle_registers() {
   return BLOCK > kBlock ? N1 <= 16 : N1 * NF <= 72;   // (short blocks as kBlock)
 }
 
-// Block -> tile map of the x and y passes: blocks go to the eight XCDs in turn,
-// and each XCD is given an eighth of the tiles in a row, a slab of tau planes.
-// An x pass and the y pass before or after it then work on the same slab in
-// the same XCD, whose L2 (4 MB) still holds it while the state is small: 64^3
-// and two fields, x, y, tau, y passes of a step pair: 27.0 -> 23.4 us; 96 x 96
-// x 64: 50.0 -> 44.9; 128 x 128 x 64: 61.2 -> 54.3; runs of 128^3 and three
-// fields (6 MB per XCD) 1753 -> 1678 us.  Not beyond 4M points a field, whose
-// slabs are several times the L2 (256^3: 5296 -> 5469 us on all its tiles), nor
-// with less than a plane per XCD (CW 128 x 128: 561 -> 579).  (tau lines cross
-// every slab.)
+// Block -> tile map of the x and y passes (slab_tiles says when): blocks go to
+// the eight XCDs in turn, and each XCD is given an eighth of the tiles in a
+// row, a slab of tau planes.  An x pass and the y pass before or after it then
+// work on the same slab in the same XCD, whose L2 still holds part of it.
+// (tau lines cross every slab.)  nt, which decides nothing here, is looked at
+// beside the flag, which lies in another line of the launch's arguments: both
+// lines are then asked for at once (one after the other cost a pass of few
+// waves 0.3 us).
 template <class Args>
 __device__ __forceinline__ unsigned slab_tile(const Args& args, unsigned bx) {
-  if (args.nt < 8 || unsigned(args.nx) * unsigned(args.ny) * unsigned(args.nt) > (1u << 22)) return bx;
+  if (args.nt < 8 || !args.slab) return bx;
   const unsigned per_xcd = gridDim.x / 8u;
   return bx < 8u * per_xcd ? bx % 8u * per_xcd + bx / 8u : bx;   // (the last few tiles as they come)
 }

@@ -121,6 +121,22 @@ inline unsigned tile_multiplier(unsigned tiles) {
   }
 }
 
+// Whether the x and y passes of a plan's shape take their tiles in slabs
+// (slab_tile) where they follow one another (xy_neighbours).  They share an
+// XCD's L2 (4 MB) while the state is small: merged pairs, 16 steps, without /
+// with slabs: two fields, 128 x 128 x 64: 437 / 431 us; 96 x 128 x 128: 553 /
+// 502; 128^3: 583 / 554; 192 x 128 x 128: 830 / 819; three fields, 128^3: 830 /
+// 822; 192 x 128 x 128: 1210 / 1173; literal, 64 x 64 x 1024 and two fields,
+// 8 steps: 1003 / 942; batches of 64^3 and two fields, 2: 308 / 265; 8: 529 /
+// 501; 16: 891 / 897.  Not beyond 4M points (96 x 256 x 256: 1509 / 1525; 192^3:
+// 2058 / 2036; 256^3 5296 / 5469), nor with tau passes between x and y (128^3,
+// order 3, two fields: 593 / 610), nor with less than a plane per XCD (CW 128 x
+// 128: 561 / 579).  Between 3M and 4M points the two are within 1 % but for
+// lengths of 192 and long tau axes.
+inline bool slab_tiles(const brahms_plan_s& p) {
+  return p.nt >= 8 && (long long)p.nx * p.ny * p.nt <= (1LL << 22);
+}
+
 // Where one z-step reads and writes: the first pass reads `in` and writes
 // `out`, the other two passes work in place on `out`; when `pre` is given the
 // last pass also stores the input of the second RK4 half-step there.
@@ -143,6 +159,11 @@ bool merging(const brahms_plan_s& p);
 // passes, or a long tau axis between x and y) or a step of two axes, where it
 // leaves one pass of a step's three and costs nothing.
 bool fusing(const brahms_plan_s& p);
+// Whether an x and a y pass of a plan's steps follow one another: with tau
+// first or last (a long tau axis in pairs sits between them), or where a
+// merged step without pairs ends on one of them and the next begins on the
+// other.
+bool xy_neighbours(const brahms_plan_s& p);
 // The passes of one z-step in order: axis (AX_*) and RK4 mode (NL_*) of
 // each.  Three passes in general; passes along an axis of length 1 are left
 // out when they would multiply by exactly 1 (so the result is unchanged bit

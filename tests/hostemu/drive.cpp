@@ -626,6 +626,27 @@ void scenario_large_map() {
   std::printf("large map: ok\n");
 }
 
+// x and y passes take their tiles in slabs where they follow one another
+void scenario_slabs() {
+  Rng r(113);
+  auto axes = [&](Problem& p, const brahms_schedule& sc, const std::string& want) {
+    emu::g_axes.clear();
+    run_calls(p, sc, {2});
+    if (emu::g_axes != want) emu::die("slabs: axes " + emu::g_axes + ", not " + want);
+  };
+  Problem p = make_problem(r, 16, 12, 8, 2, 2, false, 0.7);
+  axes(p, schedule(0), "XYtYX");
+  axes(p, schedule(3), "ytxty");               // (a tau pass between x and y)
+  axes(p, schedule(2, 0, 1), "XtYXtY");        // (merged: one step's y, the next one's x)
+  axes(p, schedule(2, 0, 1, 1), "xtytx");
+  Problem lt = make_problem(r, 4, 2, 512, 2, 2, false, 0.7);
+  axes(lt, schedule(0), "XYtttXYttt");
+  axes(lt, schedule(0, 0, 1, 1), "xtttyttt" "x");
+  Problem thin = make_problem(r, 16, 12, 6, 2, 2, false, 0.7);
+  axes(thin, schedule(0), "xytyx");            // (less than a plane per XCD)
+  std::printf("slabs: ok\n");
+}
+
 // chunks replayed from a graph, from even and odd steps: plane waves, two axes
 // and three, literal and merged; every whole chunk is a replay
 void scenario_graph_chunks() {
@@ -697,6 +718,7 @@ int main(int argc, char** argv) {
   else if (s == "splits") scenario_splits();
   else if (s == "maps") scenario_maps();
   else if (s == "large_map") scenario_large_map();
+  else if (s == "slabs") scenario_slabs();
   else if (s == "graph_chunks") scenario_graph_chunks();
   else if (s == "adjoint") scenario_adjoint();
   else {

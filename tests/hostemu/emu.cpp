@@ -436,7 +436,7 @@ void check_args(dim3 grid, const brahms::PassArgs& a) {
   int nf = 0;
   while (nf < 3 && a.f[nf] != nullptr) ++nf;
   const char ax = a.axis_off == 0 ? 'x' : (a.axis_off == a.nx ? 'y' : 't');
-  g_axes += ax;
+  g_axes += ax != 't' && a.slab ? char(ax - 'x' + 'X') : ax;
   // a linear pass of one field per block takes its field from blockIdx.z
   if (grid.z > 1 && int(grid.z) != nf) die("plain pass: gridDim.z is not the field count");
   check_pass(a, nf, "plain pass");

@@ -21,7 +21,8 @@ void clear_regions();
 
 extern long long g_launches, g_checked_passes, g_checked_tables, g_graph_launches;
 
-// The axes (x, y, t) of the plain passes run since it was last cleared.
+// The axes (x, y, t; X, Y with the tiles in slabs) of the plain passes run since
+// it was last cleared.
 extern std::string g_axes;
 
 }  // namespace emu

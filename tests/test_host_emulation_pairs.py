@@ -1,8 +1,8 @@
 """Further call sequences on the host emulation (see test_host_emulation.py):
 literal steps in pairs with a transverse map, maps whose tables hold a few
 steps, graph replays of chunks that begin with an even and with an odd
-step (plane waves, two axes, three axes, literal and merged), and the
-adjoint.
+step (plane waves, two axes, three axes, literal and merged), the x and y
+passes that take their tiles in slabs, and the adjoint.
 Plane-wave launches are checked row by row over all the steps they take, and
 adjoint passes over their states, tables and partial sums."""
 import os
@@ -24,7 +24,7 @@ def drive():
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["maps", "large_map", "graph_chunks", "adjoint"])
+@pytest.mark.parametrize("scenario", ["maps", "large_map", "slabs", "graph_chunks", "adjoint"])
 def test_scenario_under_sanitizers(drive, scenario):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:detect_stack_use_after_return=0:abort_on_error=1",
                UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
