@@ -491,24 +491,40 @@ __device__ __forceinline__ LineAddr line_addr(const Args& args, unsigned line) {
 // field loads still in flight: one memory latency instead of one per table
 // and loop trip, and no block that waits for its tables with no field load
 // outstanding (long tau passes of 128 x 128 x 1024: 11 % less time for the
-// whole step).
-template <int N, int NF, int BLOCK, bool FUSE>
+// whole step).  WRAP (a plan's linear passes of kBlock threads): threads past a
+// table's end take its entries once more, the same values to the same places.  Where their writes
+// are left out, the compiler moves the loads down into the branch, behind the
+// fields': linear passes of 128^3 points and two fields 17.1 -> 19.6 us in x,
+// 12.3 -> 13.7 in tau.  Passes with an RK4 step and batches, whose waves hide
+// that, lose 1-2 % by the added loads (16 problems of 64^3: 928 / 947), and so
+// do blocks of 512 threads (128^3, three fields: 1674 / 1717 a run).
+template <int N, int NF, int BLOCK, bool FUSE, bool WRAP = false>
 struct StageTables {
   static constexpr int TT = (N + BLOCK - 1) / BLOCK;        // table entries per thread
   static constexpr int TP = (NF * N + BLOCK - 1) / BLOCK;
   float2 tw[TT], prop[TP], tw2[FUSE ? TT : 1], prop2[FUSE ? TP : 1];
 
+  template <int SIZE>   // the table entry of a thread in round q
+  __device__ static __forceinline__ int entry(int tid, int q) {
+    const int i = tid + q * BLOCK;
+    return SIZE % BLOCK == 0 ? i : (WRAP ? i % SIZE : min(i, SIZE - 1));
+  }
+  template <int SIZE>   // and whether the thread writes one there
+  __device__ static __forceinline__ bool writes(int tid, int q) {
+    return WRAP || SIZE % BLOCK == 0 || tid + q * BLOCK < SIZE;
+  }
+
   template <class Args>
   __device__ __forceinline__ void begin(const Args& args, int field0, int tid) {
 #pragma unroll
     for (int q = 0; q < TT; ++q) {
-      const int i = min(tid + q * BLOCK, N - 1);
+      const int i = entry<N>(tid, q);
       tw[q] = args.tw[i];
       if constexpr (FUSE) tw2[q] = args.tw2[i];
     }
 #pragma unroll
     for (int q = 0; q < TP; ++q) {
-      const int k = min(tid + q * BLOCK, NF * N - 1);
+      const int k = entry<NF * N>(tid, q);
       const int i = (field0 + k / N) * args.field_stride + args.axis_off + k % N;
       prop[q] = args.prop[i];
       if constexpr (FUSE) prop2[q] = args.prop2[i];
@@ -520,17 +536,17 @@ struct StageTables {
                                       float2* s_prop2) {
 #pragma unroll
     for (int q = 0; q < TT; ++q) {
-      const int i = tid + q * BLOCK;
-      if (N % BLOCK == 0 || i < N) {
+      const int i = entry<N>(tid, q);
+      if (writes<N>(tid, q)) {
         s_tw[i] = tw[q];
         if constexpr (FUSE) s_tw2[i] = tw2[q];
       }
     }
 #pragma unroll
     for (int q = 0; q < TP; ++q) {
-      const int i = tid + q * BLOCK;
+      const int i = entry<NF * N>(tid, q);
       if (conj) prop[q].y = -prop[q].y;
-      if ((NF * N) % BLOCK == 0 || i < NF * N) {
+      if (writes<NF * N>(tid, q)) {
         s_prop[i] = prop[q];
         if constexpr (FUSE) s_prop2[i] = prop2[q];
       }
@@ -552,7 +568,7 @@ __device__ __forceinline__ void load_coefficients(const float2* nl, float2 (&co)
 // batch's descriptor is no longer known to be the same in every lane and 16
 // vector registers would hold them through the transforms.  SCALAR (three
 // fields of a batch where the registers are short: 16 values a lane, or 192 and
-// two half-steps): moved into scalar registers, else those pairs keep 8-39
+// two half-steps): moved into scalar registers, else those pairs keep 2-39
 // values of a lane in scratch memory (now 6 at most; 64 x 256 x 256, literal:
 // 3254 -> 3207 us a run).  Elsewhere there is room and the wait for them costs
 // 1-2 % (192 x 64 x 64, merged: 2100 / 2123 us).
@@ -708,7 +724,7 @@ __device__ __forceinline__ void axis_pass_body(const PassArgs& args, unsigned bx
       }
     }
   } else {
-    StageTables<N, NF, BLOCK, FUSE> st;
+    StageTables<N, NF, BLOCK, FUSE, NF == 1 && !BATCH && BLOCK == kBlock> st;
     st.begin(args, field0, tid);
     load_fields();
     st.end(args.conj != 0, tid, s_tw, s_prop, s_tw2, s_prop2);

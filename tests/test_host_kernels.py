@@ -4,6 +4,7 @@ the kernels built are those that a dispatch can reach."""
 import os
 import re
 import struct
+import subprocess
 
 import pytest
 
@@ -59,6 +60,7 @@ def kernels():
     out = {}
     for elf in _code_objects(data):
         for k in _kernels(elf):
+            k["elf"] = elf
             m = re.match(r"_ZN6brahms\d+([a-z0-9_]+?)I((?:Li\d+E)+)E", k[".name"])
             name = m.group(1) if m else k[".name"]
             args = tuple(int(v) for v in re.findall(r"Li(\d+)E", m.group(2))) if m else ()
@@ -89,3 +91,25 @@ def test_no_kernel_without_a_dispatch(kernels):
     splits = {(int(a), int(b)) for a, b in re.findall(r"X\(\d+, (\d+), (\d+)\)", first)}
     assert len(splits) == 21
     assert {args[:2] for (name, args) in kernels if name == "adjoint_pass"} == splits
+
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.mark.parametrize("split", [(16, 8), (8, 8), (12, 4), (24, 8), (9, 1)])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_tables_are_asked_for_before_the_fields(kernels, split, axis, tmp_path):
+    """Linear passes: the loads of the step's tables (global) are issued ahead
+    of those of the fields (buffer), none behind them; waiting for the tables,
+    which the first barrier needs, then does not wait for the fields."""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no disassembler")
+    k = kernels["axis_pass", (*split, axis, 1, 0, 256)]
+    path = tmp_path / "unit.elf"
+    path.write_bytes(k["elf"])
+    asm = subprocess.run([OBJDUMP, "-d", "--disassemble-symbols=" + k[".name"], str(path)], capture_output=True,
+                         text=True, check=True).stdout
+    loads = re.findall(r"\t(global_load|buffer_load|s_barrier)", asm)
+    loads = loads[:loads.index("s_barrier")]
+    assert loads.count("global_load") >= 2 and loads.count("buffer_load") == split[0]
+    assert "global_load" not in loads[loads.index("buffer_load"):]
