@@ -537,7 +537,7 @@ def main():
             if modes[k] in FUSED_MODES and rec["launches"]:
                 n_axis = {"x_pass": wl.nx, "y_pass": wl.ny, "t_pass": wl.nt}[k]
                 tf = fused_pass_flops(wl.nf, wl.points, n_axis, FUSED_MODES[modes[k]]) / (rec["avg_ms"] * 1e-3) / 1e12
-                rec.update({"bound": "alu", "TFLOPs": round(tf, 2), "frac": round(tf / FP32_PEAK_TFLOPS, 4),
+                rec.update({"bound": "latency", "TFLOPs": round(tf, 2), "frac": round(tf / FP32_PEAK_TFLOPS, 4),
                             "hbm_frac": round(rec["GBps"] / HBM_PEAK_GBS, 4)})
             elif rec["GBps"]:
                 rec.update({"bound": "hbm", "frac": round(rec["GBps"] / HBM_PEAK_GBS, 4)})
@@ -558,7 +558,8 @@ def main():
         axis_len = {"x_pass": wl.nx, "y_pass": wl.ny, "t_pass": wl.nt}[dom_members[0]]
         flops = fused_pass_flops(wl.nf, wl.points, axis_len, FUSED_MODES[modes[dom_members[0]]])
         tflops = flops / (avg_ms * 1e-3) / 1e12
-        dominant = {"kernel": dom, "axes": dom_members, "bound": "alu", "achieved": round(tflops, 2),
+        # (bound by a wave's chain of LDS round trips: near neither peak)
+        dominant = {"kernel": dom, "axes": dom_members, "bound": "latency", "achieved": round(tflops, 2),
                     "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(tflops / FP32_PEAK_TFLOPS, 4),
                     "hbm_GBps": round(achieved, 1), "algorithmic_flops_per_launch": flops,
                     "avg_launch_ms": round(avg_ms, 5), "share_of_step_time": round(dom_ms / sum(

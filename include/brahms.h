@@ -213,7 +213,9 @@ brahms_status brahms_plan_destroy(brahms_plan plan);
  *     is the same linear step; and each step's last transform, the merged RK4
  *     step and the next step's first transform are along one axis and run
  *     as one pass: two reads and writes of the fields per step instead of
- *     three.  Calls run without it while merge_halves is suspended.
+ *     three.  While merge_halves is suspended
+ *     (monitor records, snapshots) calls run literal half-steps, in pairs as
+ *     above up to each step that is looked at.
  *     BRAHMS_E_INVALID_ARG without merge_halves, BRAHMS_E_UNSUPPORTED for
  *     other step structures.
  *   split (bits 1 = x, 2 = y, 4 = tau): a line of length N = N1 N2 is
